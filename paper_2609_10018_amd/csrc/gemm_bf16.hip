@@ -193,7 +193,7 @@ __device__ __forceinline__ LnStat ln_of_group8(const float* v, bool valid, bool 
 // 16-byte load) whose pair index is i = first, first + step, ... <
 // ceil(nseg / 2), four loads in flight at a time.  Branch-free: a pair past
 // the last re-reads pair 0, and a segment past the last (n_j <= 0) merges as
-// an empty one.
+// an empty one whatever its slot holds (nothing writes it).
 __device__ __forceinline__ void ln_sums(const float2* row, int K, int first, int step, LnStat& st) {
   const int nseg = (K + 63) >> 6, npair = (nseg + 1) >> 1;
   for (int i0 = first; i0 < npair; i0 += 4 * step) {
@@ -210,7 +210,7 @@ __device__ __forceinline__ void ln_sums(const float2* row, int K, int first, int
       for (int h = 0; h < 2; ++h) {
         const int nj = i < npair ? min(64, K - 64 * (2 * i + h)) : 0;
         const float nb = (float)max(nj, 0);
-        ln_merge(st, nb, q[t][2 * h] * __builtin_amdgcn_rcpf(fmaxf(nb, 1.0f)),
+        ln_merge(st, nb, nj > 0 ? q[t][2 * h] * __builtin_amdgcn_rcpf(nb) : 0.0f,
                  nj > 0 ? q[t][2 * h + 1] : 0.0f);
       }
     }

@@ -154,3 +154,23 @@ def test_linear_ln_argument_checks():
     with pytest.raises(ffi.ElastoError):        # odd stats_ld
         ffi.op_linear_ln(ffi.EPI_BIAS, A, 64, W, 64, C, 8, b, 8, 8, 64, 1, stats_in=st,
                          colsum=b)
+
+
+def test_unwritten_statistics_slots_do_not_matter():
+    """An odd number of segments leaves the last slot of a row unwritten: what
+    memory happens to hold there (a NaN) is no part of the row's statistics."""
+    M, d, N = 300, 192, 64
+    g = torch.Generator(device="cuda").manual_seed(0)
+    x = torch.randn(M, d, generator=g, device="cuda").bfloat16()
+    v = (torch.randn(N, d, generator=g, device="cuda") * 0.1).bfloat16()
+    seg = x.double().reshape(M, 3, 64)
+    st = torch.full((M, 4, 2), float("nan"), device="cuda")
+    st[:, :3, 0] = seg.sum(2).float()
+    st[:, :3, 1] = ((seg - seg.mean(2, keepdim=True)) ** 2).sum(2).float()
+    bias, col = torch.zeros(N, device="cuda"), v.double().sum(1).float()
+    y = torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
+    ffi.op_linear_ln(ffi.EPI_BIAS, x, d, v, d, y, N, bias, M, N, d, 4, stats_in=st, colsum=col)
+    u = torch.nn.functional.layer_norm(x.double(), (d,), eps=1e-6)
+    z = u @ v.double().t()
+    # bf16 rounding of the result and a folded product of 192 terms.
+    assert float((y.double() - z).abs().max()) < 2.0 ** -7 * float(z.abs().max())
