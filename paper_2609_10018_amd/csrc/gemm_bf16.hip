@@ -40,6 +40,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_small.h"
 #include "kernels.h"
 
 namespace elasto {
@@ -1304,6 +1305,105 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent(Params p) {
   wait_vm_lds<0>();
 }
 
+// Epilogue of one 8-column chunk (columns col .. col + 7 of row `row` < M)
+// from its product sums v, for the kernels that hold results row-wise.  rs:
+// the row's folded-LayerNorm factors.  The 8 lanes of an aligned group hold
+// the 8 chunks of a 64-column segment of one row (producers' statistics), and
+// all 8 call this, also for columns past N.
+template <Epi E>
+__device__ __forceinline__ void epilogue_chunk(const Params& p, int row, int col, float (&v)[8],
+                                               float2 rs) {
+  const bool col_in = col < p.N, full = col + 8 <= p.N;
+  const int left = p.N - col;
+  if constexpr (E == Epi::BiasF32) {
+    if (!col_in) return;
+    if (p.bias != nullptr) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += e < left ? p.bias[col + e] : 0.0f;
+    }
+    store_f32x8(static_cast<float*>(p.C) + (int64_t)row * p.ldc + col, v, full, left);
+  } else if constexpr (E == Epi::Bias || E == Epi::BiasGelu || E == Epi::GeluBwd) {
+    if (!col_in) return;
+    uint16_t* cp = static_cast<uint16_t*>(p.C) + (int64_t)row * p.ldc + col;
+    if constexpr (E == Epi::GeluBwd) {
+      const uint16_t* ap = p.aux + (int64_t)row * p.ldaux + col;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        v[e] = e < left ? v[e] * gelu_poly_grad(bf16_to_f32(ap[e])) : 0.0f;
+    } else {
+      float bv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) bv[e] = p.bias != nullptr && e < left ? p.bias[col + e] : 0.0f;
+      if (p.ln_in != nullptr) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float cs = e < left ? p.ln_colsum[col + e] : 0.0f;
+          v[e] = fmaf(v[e], rs.x, fmaf(rs.y, cs, bv[e]));
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += bv[e];
+      }
+      if constexpr (E == Epi::BiasGelu) {
+        if (p.aux != nullptr) store_bf16x8(p.aux + (int64_t)row * p.ldaux + col, v, full, left);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = gelu_poly(v[e]);
+      } else if (p.relu) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.0f);
+      }
+    }
+    store_bf16x8(cp, v, full, left);
+  } else {
+    static_assert(E == Epi::BiasResid || E == Epi::Patch, "epilogues");
+    if (col_in) {
+      uint16_t* cp = static_cast<uint16_t*>(p.C) + (int64_t)row * p.ldc + col;
+      float bv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) bv[e] = p.bias != nullptr && e < left ? p.bias[col + e] : 0.0f;
+      float* cls_row = nullptr;
+      if (p.ccls != nullptr) {
+        const int bi = row / p.tokens;
+        if (row == bi * p.tokens) cls_row = p.ccls + (int64_t)bi * p.N + col;
+      }
+      if constexpr (E == Epi::Patch) {  // class rows (t == 0) take cls + pos[0], no product
+        const int t = row % p.tokens;
+        const float* pp = p.pos + (int64_t)t * p.ldpos + col;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          v[e] = e < left ? (t == 0 ? p.cls[col + e] : v[e] + bv[e]) + pp[e] : 0.0f;
+      } else if (cls_row != nullptr) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = e < left ? cls_row[e] + (v[e] + bv[e]) : 0.0f;
+      } else {
+        const uint16_t* rp = p.res != nullptr ? p.res + (int64_t)row * p.ldres + col : cp;
+        if (full) {
+          const u32x4 x = *reinterpret_cast<const u32x4*>(rp);
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            v[e] = __uint_as_float((e & 1) ? (x[e >> 1] & 0xffff0000u) : (x[e >> 1] << 16)) +
+                   (v[e] + bv[e]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = e < left ? bf16_to_f32(rp[e]) + (v[e] + bv[e]) : 0.0f;
+        }
+        if (p.relu) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.0f);
+        }
+      }
+      if (cls_row != nullptr) store_f32x8(cls_row, v, full, left);
+      if (cls_row == nullptr || p.ln_out != nullptr) store_bf16x8(cp, v, full, left);
+    }
+    if (p.ln_out != nullptr) {
+      const LnStat ls = ln_of_group8(v, col_in, (p.N & 63) == 0);
+      const int seg = col >> 6;
+      if ((col & 63) == 0 && col_in)
+        p.ln_out[(int64_t)row * p.ln_ld + seg] = make_float2(ls.n * ls.mean, ls.m2);
+    }
+  }
+}
+
 // Split-K epilogue.  A GEMM whose tiles would occupy few of the CUs (small M:
 // batch-1 and batch-8 forwards) runs as ksplit K-chunks of the BiasF32 kernel
 // writing fp32 partial products, then this kernel sums each output's partials
@@ -1315,23 +1415,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent(Params p) {
 struct SplitEpi {
   const float* part;   // ksplit slices of [M][ldp] fp32
   int64_t ldp, slice;  // row stride of a slice (a multiple of 8), elements per slice
-  int ksplit, M, N, K, cpr;
-  void* C;
-  int64_t ldc;
-  const float* bias;
-  const uint16_t* res;  // BiasResid residual (nullptr: C)
-  int64_t ldres;
-  float* ccls;
-  int tokens;
-  float2* ln_out;
-  const float2* ln_in;
-  int64_t ln_ld;
-  const float* ln_colsum;
-  float ln_eps;
+  int ksplit, cpr;
 };
 
 template <Epi E>
-__global__ __launch_bounds__(64) void splitk_epilogue_kernel(SplitEpi q) {
+__global__ __launch_bounds__(64) void splitk_epilogue_kernel(Params p, SplitEpi q) {
   static_assert(E == Epi::Bias || E == Epi::BiasGelu || E == Epi::BiasResid, "split-K epilogues");
   const int64_t g = (int64_t)blockIdx.x * 64 + threadIdx.x;
   const int row = (int)(g / q.cpr), cc = (int)(g - (int64_t)row * q.cpr);
@@ -1340,24 +1428,23 @@ __global__ __launch_bounds__(64) void splitk_epilogue_kernel(SplitEpi q) {
   // every thread of the row.
   float2 rs = make_float2(0.0f, 0.0f);
   if constexpr (E == Epi::Bias || E == Epi::BiasGelu) {
-    if (q.ln_in != nullptr) {
+    if (p.ln_in != nullptr) {
       __shared__ float2 fac[64 / 8 + 1];
       const int r0 = (int)((int64_t)blockIdx.x * 64 / q.cpr);
       const int r = r0 + (int)threadIdx.x;
-      if (threadIdx.x <= 64 / 8 && r < q.M && (int64_t)r * q.cpr < (int64_t)blockIdx.x * 64 + 64) {
+      if (threadIdx.x <= 64 / 8 && r < p.M && (int64_t)r * q.cpr < (int64_t)blockIdx.x * 64 + 64) {
         LnStat st{0.0f, 0.0f, 0.0f};
-        ln_sums(q.ln_in + (int64_t)r * q.ln_ld, q.K, 0, 1, st);
-        fac[threadIdx.x] = ln_factors(st, q.ln_eps);
+        ln_sums(p.ln_in + (int64_t)r * p.ln_ld, p.K, 0, 1, st);
+        fac[threadIdx.x] = ln_factors(st, p.ln_eps);
       }
       __syncthreads();
-      if (row < q.M) rs = fac[row - r0];
+      if (row < p.M) rs = fac[row - r0];
     }
   }
-  if (row >= q.M) return;  // whole 8-lane groups: cpr is a multiple of 8
+  if (row >= p.M) return;  // whole 8-lane groups: cpr is a multiple of 8
   const int col = cc * 8;
-  const bool col_in = col < q.N, full = col + 8 <= q.N;
   float v[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-  if (col_in) {
+  if (col < p.N) {
     const float* pp = q.part + (int64_t)row * q.ldp + col;
     for (int c0 = 0; c0 < q.ksplit; c0 += 8) {
       f32x4 t[8][2];
@@ -1378,66 +1465,73 @@ __global__ __launch_bounds__(64) void splitk_epilogue_kernel(SplitEpi q) {
         }
     }
   }
-  float bv[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) bv[e] = col + e < q.N ? q.bias[col + e] : 0.0f;
-  uint16_t* cp = static_cast<uint16_t*>(q.C) + (int64_t)row * q.ldc + col;
-  if constexpr (E == Epi::Bias || E == Epi::BiasGelu) {
-    if (!col_in) return;
-    if (q.ln_in != nullptr) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float cs = col + e < q.N ? q.ln_colsum[col + e] : 0.0f;
-        v[e] = fmaf(v[e], rs.x, fmaf(rs.y, cs, bv[e]));
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] += bv[e];
-    }
-    if constexpr (E == Epi::BiasGelu) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = gelu_poly(v[e]);
-    }
-    store_bf16x8(cp, v, full, q.N - col);
-  } else {
-    float st[8];
-    bool st_ok = false;
-    if (col_in) {
-      float* cls_row = nullptr;
-      if (q.ccls != nullptr) {
-        const int bi = row / q.tokens;
-        if (row == bi * q.tokens) cls_row = q.ccls + (int64_t)bi * q.N + col;
-      }
-      if (cls_row != nullptr) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = col + e < q.N ? cls_row[e] + (v[e] + bv[e]) : 0.0f;
-        store_f32x8(cls_row, v, full, q.N - col);
-        if (q.ln_out != nullptr) store_bf16x8(cp, v, full, q.N - col);
-      } else {
-        const uint16_t* rp = q.res != nullptr ? q.res + (int64_t)row * q.ldres + col : cp;
-        if (full) {
-          const u32x4 x = *reinterpret_cast<const u32x4*>(rp);
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            v[e] = __uint_as_float((e & 1) ? (x[e >> 1] & 0xffff0000u) : (x[e >> 1] << 16)) +
-                   (v[e] + bv[e]);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            v[e] = col + e < q.N ? bf16_to_f32(rp[e]) + (v[e] + bv[e]) : 0.0f;
+  epilogue_chunk<E>(p, row, col, v, rs);
+}
+
+// GEMM for launches of few tiles (gemm_small.h).  Bound: one memory latency, a
+// workgroup's stream of operands (115 GB/s) and the launch.  us before (128x128
+// tiles, or two launches with K split) and now: 197 rows, 1152 x 768 11.6, 3.9;
+// 3072 x 768 11.8, 6.8; 768 x 1536 19.8, 5.0; 768 x 3072 33.5, 6.5; 8 rows,
+// 1000 x 768 10.2, 3.3.  ViT-B, one image, half-width mode: 803, 394.
+template <Epi E, int TMB, int TNB, int D>
+__global__ __launch_bounds__(256) void gemm_bf16_small(Params p) {
+  using T = SmallTile<uint16_t, TMB, TNB, 4, D>;
+  constexpr bool LN_CONSUMER = E == Epi::Bias || E == Epi::BiasGelu;
+  __shared__ __attribute__((aligned(1024))) char smem[T::SMEM];
+  __shared__ float2 fac[LN_CONSUMER ? T::R : 1];
+  int tm, tn;
+  small_tile_of((p.M + T::R - 1) / T::R, &tm, &tn);
+  const int m0 = tm * T::R, n0 = tn * T::CN;
+  T::run(
+      smem, p.K,
+      [&](int i, int r) -> const uint16_t* {
+        if (i >= T::ABLK) return p.W + (int64_t)min(n0 + r, p.N - 1) * p.ldw;
+        const int gm = min(m0 + r, p.M - 1);
+        if constexpr (E == Epi::Patch) {
+          const int bi = gm / p.tokens, t = gm - bi * p.tokens;
+          const int n = t > 0 ? t - 1 : 0, py = n / p.grid, px = n - py * p.grid;
+          return p.img + ((int64_t)bi * p.chans * p.img_size + (int64_t)py * p.patch) * p.img_size +
+                 px * p.patch;
         }
-        store_bf16x8(cp, v, full, q.N - col);
-      }
+        return p.A + (int64_t)gm * p.lda;
+      },
+      [&](int i, int k) -> int64_t {  // im2col for patches
+        if constexpr (E == Epi::Patch) {
+          if (i < T::ABLK) {
+            const int pp = p.patch * p.patch, c = k / pp, rem = k - c * pp, ii = rem / p.patch;
+            return ((int64_t)c * p.img_size + ii) * p.img_size + (rem - ii * p.patch);
+          }
+        }
+        return k;
+      },
+      [](int, const uint16_t* q, int) { return *reinterpret_cast<const u32x4*>(q); },
+      [&] {
+        // Folded LayerNorm: the factors of the tile's rows, two lanes a row.
+        if constexpr (LN_CONSUMER) {
+          if (p.ln_in != nullptr && threadIdx.x >= 192) {
+            const int lane = threadIdx.x & 63;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) st[e] = v[e];
-      st_ok = true;
+            for (int h = 0; h < (T::R + 31) / 32; ++h) {
+              const int r = min(32 * h + (lane >> 1), T::R - 1);
+              LnStat st{0.0f, 0.0f, 0.0f};
+              ln_sums(p.ln_in + (int64_t)min(m0 + r, p.M - 1) * p.ln_ld, p.K, lane & 1, 2, st);
+              ln_merge_dpp<kDppXor1>(st);
+              if ((lane & 1) == 0) fac[r] = ln_factors(st, p.ln_eps);
+            }
+          }
+        }
+      });
+  constexpr int CPR = T::CN / 8;
+  for (int c = threadIdx.x; c < T::R * CPR; c += 256) {
+    const int rl = c / CPR, cl = (c - rl * CPR) * 8;
+    if (m0 + rl >= p.M) continue;  // the same row for every lane of an 8-lane group
+    float v[8];
+    T::sum8(smem, rl, cl, v);
+    float2 rs = make_float2(0.0f, 0.0f);
+    if constexpr (LN_CONSUMER) {
+      if (p.ln_in != nullptr) rs = fac[rl];
     }
-    if (q.ln_out != nullptr) {
-      const LnStat ls = ln_of_group8(st, st_ok, (q.N & 63) == 0);
-      const int seg = cc >> 3;
-      if ((cc & 7) == 0 && 64 * seg < q.N)
-        q.ln_out[(int64_t)row * q.ln_ld + seg] = make_float2(ls.n * ls.mean, ls.m2);
-    }
+    epilogue_chunk<E>(p, m0 + rl, n0 + cl, v, rs);
   }
 }
 
@@ -1457,6 +1551,32 @@ hipError_t launch_cfg(const Params& p0, int row0, hipStream_t s) {
                      dim3((unsigned)blocks, (unsigned)(p.ksplit > 1 ? p.ksplit : 1)),
                      dim3(64 * WM * WN), ln_consumer ? BM * 8 : 0, s, p);
   return hipGetLastError();
+}
+
+// Whether the kernel for few tiles takes the launch (small_pick), and its
+// launch.  A producer of LayerNorm statistics needs tiles of 64 columns.
+constexpr SmallShape kSmall[] = {{1, 2}, {2, 2}, {2, 4}, {4, 4}};
+constexpr SmallShape kSmallSegments[] = {{1, 4}, {2, 4}, {4, 4}};
+inline int small_choice(const Params& p) {
+  return p.ln_out != nullptr ? small_pick(kSmallSegments, p.M, p.N) : small_pick(kSmall, p.M, p.N);
+}
+template <Epi E, int TMB, int TNB, int D>
+hipError_t launch_small_cfg(const Params& p, hipStream_t s) {
+  const int blocks = ((p.M + 16 * TMB - 1) / (16 * TMB)) * ((p.N + 16 * TNB - 1) / (16 * TNB));
+  hipLaunchKernelGGL((gemm_bf16_small<E, TMB, TNB, D>), dim3((unsigned)blocks), dim3(256), 0, s, p);
+  return hipGetLastError();
+}
+template <Epi E>
+hipError_t launch_small(const Params& p, int choice, hipStream_t s) {
+  if (choice == 0) {
+    if constexpr (E == Epi::BiasResid || E == Epi::Patch) {
+      if (p.ln_out != nullptr) return launch_small_cfg<E, 1, 4, 3>(p, s);
+    }
+    return launch_small_cfg<E, 1, 2, 3>(p, s);
+  }
+  if (p.ln_out != nullptr) ++choice;
+  if (choice == 1) return launch_small_cfg<E, 2, 2, 3>(p, s);
+  return choice == 2 ? launch_small_cfg<E, 2, 4, 2>(p, s) : launch_small_cfg<E, 4, 4, 2>(p, s);
 }
 
 // Compute units of the current device (cached per device).
@@ -1565,6 +1685,12 @@ hipError_t launch_forced(const Params& p, hipStream_t s) {
 template <Epi E, bool CONV = false>
 hipError_t launch_epi(const Params& p, hipStream_t s) {
   if (p.plan != 0) return launch_forced<E, CONV>(p, s);
+  if constexpr (!CONV) {
+    if (p.ksplit <= 1) {
+      const int small = small_choice(p);
+      if (small >= 0) return launch_small<E>(p, small, s);
+    }
+  }
   // Pick the launch plan that keeps the chip busiest.  Estimated time is the
   // number of rounds of concurrent workgroups (one per CU) times the relative
   // cost of one tile.  Besides single launches of one tile shape there is a
@@ -1703,25 +1829,10 @@ hipError_t launch_split(const Params& p, float* ws, int ksplit, int kchunk, hipS
   q.ldp = ldp;
   q.slice = pp.c_split;
   q.ksplit = ksplit;
-  q.M = p.M;
-  q.N = p.N;
-  q.K = p.K;
   q.cpr = (int)((p.N + 63) / 64 * 8);
-  q.C = p.C;
-  q.ldc = p.ldc;
-  q.bias = p.bias;
-  q.res = p.res;
-  q.ldres = p.ldres;
-  q.ccls = p.ccls;
-  q.tokens = p.tokens;
-  q.ln_out = p.ln_out;
-  q.ln_in = p.ln_in;
-  q.ln_ld = p.ln_ld;
-  q.ln_colsum = p.ln_colsum;
-  q.ln_eps = p.ln_eps;
   const int64_t threads = (int64_t)p.M * q.cpr;
   hipLaunchKernelGGL(splitk_epilogue_kernel<E>, dim3((unsigned)((threads + 63) / 64)), dim3(64),
-                     0, s, q);
+                     0, s, p, q);
   return hipGetLastError();
 }
 
@@ -1792,10 +1903,10 @@ hipError_t launch_gemm_bf16(Epi epi, const GemmArgs& a, hipStream_t s) {
                         (epi == Epi::Bias || epi == Epi::BiasGelu || epi == Epi::BiasResid);
   int ksplit = 1, kchunk = 0;
   if (a.plan >= kSplitPlan0) {
-    if (!split_ok) return hipErrorNotSupported;
+    if (!split_ok || small_choice(p) >= 0) return hipErrorNotSupported;
     ksplit = forced_split(p, a.ws_bytes, kSplitChunks[a.plan - kSplitPlan0], &kchunk);
     if (ksplit < 2) return hipErrorNotSupported;
-  } else if (a.plan == 0 && split_ok) {
+  } else if (a.plan == 0 && split_ok && small_choice(p) < 0) {
     ksplit = split_plan(p, a.ws_bytes, &kchunk);
   }
   if (ksplit > 1) {

@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_small.h"
 #include "kernels.h"
 
 namespace elasto {
@@ -240,6 +241,57 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(P32 p) {
       store_column<E>(p, m0 + wm + 32 * i + 4 * lg, n0 + wn + 32 * j + lr, bias[j], acc[i][j]);
 }
 
+// GEMM for launches of few tiles (gemm_small.h): 16-byte aligned rows.
+template <Epi E, int TMB, int TNB>
+__global__ __launch_bounds__(256) void gemm_f32_small(P32 p) {
+  using T = SmallTile<float, TMB, TNB, 4, 3>;
+  __shared__ __attribute__((aligned(1024))) char smem[T::SMEM];
+  int tm, tn;
+  small_tile_of((p.M + T::R - 1) / T::R, &tm, &tn);
+  const int64_t m0 = (int64_t)tm * T::R;
+  const int n0 = tn * T::CN;
+  T::run(
+      smem, p.K,
+      [&](int i, int r) {
+        return i < T::ABLK ? p.A + std::min(m0 + r, p.M - 1) * p.lda
+                           : p.W + (int64_t)std::min(n0 + r, p.N - 1) * p.ldw;
+      },
+      [](int, int k) { return k; },
+      [&](int, const float* q, int k) {
+        return __builtin_bit_cast(u32x4, k + 4 <= p.K ? load_k4<true, true>(q, 0, 4)
+                                                      : load_k4<false, false>(q, 0, p.K - k));
+      },
+      [] {});
+  constexpr int CPR = T::CN / 8;
+  for (int c = threadIdx.x; c < T::R * CPR; c += 256) {
+    const int rl = c / CPR, cl = (c - rl * CPR) * 8;
+    const int64_t row = m0 + rl;
+    if (row >= p.M) continue;
+    float v[8], add[8], bias[8];
+    T::sum8(smem, rl, cl, v);
+    float* const out = static_cast<float*>(p.C) + row * p.ldc + n0 + cl;
+    const int left = p.N - (n0 + cl);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      bias[e] = e < left ? p.bias[n0 + cl + e] : 0.0f;
+      add[e] = E == Epi::BiasResid && e < left ? out[e] : 0.0f;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if (e >= left) break;
+      const float z = v[e] + bias[e];
+      out[e] = E == Epi::BiasGelu ? gelu_erf(z) : E == Epi::BiasResid ? add[e] + z : z;
+    }
+  }
+}
+
+template <Epi E, int TMB, int TNB>
+hipError_t launch_small(const P32& p, hipStream_t s) {
+  const int64_t blocks = (p.M + 16 * TMB - 1) / (16 * TMB) * ((p.N + 16 * TNB - 1) / (16 * TNB));
+  hipLaunchKernelGGL((gemm_f32_small<E, TMB, TNB>), dim3((unsigned)blocks), dim3(256), 0, s, p);
+  return hipGetLastError();
+}
+
 template <Epi E, int BM, int BN, bool VEC>
 hipError_t launch_tile(P32 p, hipStream_t s) {
   p.tiles_n = (p.N + BN - 1) / BN;
@@ -255,6 +307,14 @@ hipError_t launch(const P32& p, hipStream_t s) {
   // larger where they are equal: 8000 x 3072 x 3072 takes 1180 us with 128x128
   // tiles and 1224 with 64x64, 6304 x 1536 x 384 107 and 79 us, 6304 x 384 x
   // 384 34 and 25 us.
+  if constexpr (VEC && E != Epi::Patch) {
+    constexpr SmallShape kSmall[] = {{1, 1}, {1, 2}, {2, 2}};
+    switch (small_pick(kSmall, p.M, p.N)) {
+      case 0: return launch_small<E, 1, 1>(p, s);
+      case 1: return launch_small<E, 1, 2>(p, s);
+      case 2: return launch_small<E, 2, 2>(p, s);
+    }
+  }
   constexpr int64_t kCUs = 256;
   auto load = [&](int bm, int bn) {
     const int64_t t = (p.M + bm - 1) / bm * ((p.N + bn - 1) / bn);

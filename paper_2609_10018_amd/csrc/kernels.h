@@ -88,14 +88,18 @@ struct GemmArgs {
 // 2 256x128, 3 128x128, 4 256x64, 5 128x128 with four LDS stages (bf16
 // Bias / BiasGelu / BiasResid, no implicit convolution, K a multiple of 64
 // and >= 256), 6 the persistent 256x256 kernel (where the planner may use
-// it).  Every plan walks K in the same order with the same MFMA
+// it).  These plans walk K in the same order with the same MFMA
 // instruction, so for a GEMM with no LayerNorm work (ln_in, ln_out) and no
 // class-token rows (ccls) the outputs are bit-identical whatever the plan.
+// Plan 0 takes the kernel of gemm_small.h for launches whose 64x64 tiles (or
+// smaller ones) all run at once; its sums are split over four waves, so its
+// bits differ from the other plans', but not with the launch's size.
 // Plans kSplitPlan0 + i split K into about kSplitChunks[i] chunks (bf16 Bias /
 // BiasGelu / BiasResid with a workspace, where the 128x128 tiles would fill
-// under half the CUs; the partials are summed in chunk order, so the bits
-// differ from the unsplit plans').  A forced tile plan (1-6) never splits;
-// plan 0 splits where the planner's cost model says so.
+// under half the CUs and plan 0 has no one-round kernel; the partials are
+// summed in chunk order, so the bits differ from the unsplit plans').  A
+// forced tile plan (1-6) never splits; plan 0 splits where the planner's cost
+// model says so.
 constexpr int kSplitPlan0 = 7;
 constexpr int kSplitChunks[] = {2, 3, 4, 6, 8, 12, 16};
 constexpr int kTilePlans = kSplitPlan0 + (int)(sizeof(kSplitChunks) / sizeof(kSplitChunks[0]));
