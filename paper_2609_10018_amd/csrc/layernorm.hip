@@ -155,13 +155,16 @@ hipError_t launch_ln(const uint16_t* x, int64_t x_stride, const float* xcls, int
 
 // Weights of a LayerNorm folded into the following linear layer: one wave
 // per output row n.  Sums over the row accumulate in fp64 (the folded column
-// sum is of the bf16-rounded products the GEMM multiplies).
+// sum is of the bf16-rounded products the GEMM multiplies).  NW: most widths
+// this launch sums for; with one width (no elastic embedding) the sums for the
+// other 15 were most of its time (3072 x 768: 26 us, now 10 us).
 constexpr int kFoldMaxWidths = 16;
 struct FoldWidths {
   int n;
   int e[kFoldMaxWidths];
 };
 
+template <int NW>
 __global__ __launch_bounds__(256) void ln_fold_kernel(const uint16_t* __restrict__ W, int N, int D,
                                                       const float* __restrict__ gamma,
                                                       const float* __restrict__ beta,
@@ -174,23 +177,23 @@ __global__ __launch_bounds__(256) void ln_fold_kernel(const uint16_t* __restrict
   if (n >= N) return;
   const uint16_t* w = W + (int64_t)n * D;
   uint16_t* wf = Wf + (int64_t)n * D;
-  double sw[kFoldMaxWidths], sb[kFoldMaxWidths];
+  double sw[NW], sb[NW];
 #pragma unroll
-  for (int i = 0; i < kFoldMaxWidths; ++i) sw[i] = sb[i] = 0.0;
+  for (int i = 0; i < NW; ++i) sw[i] = sb[i] = 0.0;
   for (int k = lane; k < D; k += 64) {
     const float wv = bf16_to_f32(w[k]);
     const uint16_t f = f32_to_bf16(gamma[k] * wv);
     wf[k] = f;
     const double fv = (double)bf16_to_f32(f), bv = (double)beta[k] * (double)wv;
 #pragma unroll
-    for (int i = 0; i < kFoldMaxWidths; ++i)
+    for (int i = 0; i < NW; ++i)
       if (i < wd.n && k < wd.e[i]) {
         sw[i] += fv;
         sb[i] += bv;
       }
   }
 #pragma unroll
-  for (int i = 0; i < kFoldMaxWidths; ++i) {
+  for (int i = 0; i < NW; ++i) {
     if (i >= wd.n) break;
     double a = sw[i], c = sb[i];
 #pragma unroll
@@ -245,10 +248,14 @@ hipError_t launch_ln_fold(const void* W, int N, int D, const float* gamma, const
     if (widths[i] < 1 || widths[i] > D) return hipErrorInvalidValue;
     wd.e[i] = widths[i];
   }
-  hipLaunchKernelGGL(ln_fold_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, s,
-                     static_cast<const uint16_t*>(W), N, D, gamma, beta, bias, wd,
-                     static_cast<uint16_t*>(Wf), colsum, cbias, ldv);
-  return hipGetLastError();
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, s,
+                       static_cast<const uint16_t*>(W), N, D, gamma, beta, bias, wd,
+                       static_cast<uint16_t*>(Wf), colsum, cbias, ldv);
+    return hipGetLastError();
+  };
+  if (nw == 1) return go(ln_fold_kernel<1>);
+  return nw <= 4 ? go(ln_fold_kernel<4>) : go(ln_fold_kernel<kFoldMaxWidths>);
 }
 
 }  // namespace elasto
