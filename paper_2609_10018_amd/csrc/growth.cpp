@@ -11,13 +11,16 @@
 //   final LN backward into the fp32 stream gradient dX (class rows);
 //   per layer, last to first:
 //     fc2:  dh = (dX W2[:, :m]) * GELU'(pre)     (GEMM, GELU' epilogue)
-//           dW2[:, mp:m] = dX^T g[:, mp:m]        (transposes + split-K GEMM)
+//           dW2[:, mp:m] = dX^T g[:, mp:m]
 //     fc1:  du = dh W1[:m]; dW1[mp:m] = dh[:, mp:m]^T u2; db1 = column sums
 //     LN2 backward: dX += LN'(du)
 //     proj: do = dX WO[:, :64h]; dWO[:, 64hp:64h] = dX^T o[:, 64hp:64h]
 //     attention backward -> dqkv
 //     qkv:  du = dqkv WQKV[:192h]; dWQKV[192hp:192h] = dqkv[:, ...]^T u1; dbqkv
+//     the layer's four weight and two bias gradients in one launch
 //     LN1 backward: dX += LN'(du)
+//   (the weights, which no step changes before its update, are transposed in
+//   one launch at the start)
 //   |G (.) grad| over the gradients of the re-introduced slices (which is all
 //   G keeps), clip factor, masked update of fp32 masters -> packed bf16.
 // Weight gradients of shared (frozen) weights are never formed: with the
@@ -54,6 +57,8 @@ struct ModePlan {
   int64_t grad_floats = 0;
   GrowthSlice* slices = nullptr;  // device
   int nslices = 0;
+  TransposeJob* jobs = nullptr;   // device: the matrices the mode's backward reads transposed
+  int njobs = 0, job_tiles = 0;
 };
 
 }  // namespace
@@ -62,16 +67,20 @@ struct elasto_growth_s {
   elasto_handle_s* h = nullptr;
   int device = 0;
   int max_batch = 0;
-  int64_t Mmax = 0, Mp8 = 0;
+  int64_t Mmax = 0;
   uint8_t* mem = nullptr;
   int64_t mem_bytes = 0;
   float* master = nullptr;
   std::vector<uint16_t*> X, Xm, u1, u2, qkv, o, pre, gact;
-  uint16_t *ucls = nullptr, *dlog = nullptr, *ducls = nullptr, *dXb = nullptr, *du = nullptr,
-           *dh = nullptr, *dout = nullptr, *dqkv = nullptr, *TA = nullptr, *TB = nullptr,
-           *WT = nullptr, *WhT = nullptr;
-  float *logits = nullptr, *rowloss = nullptr, *dX = nullptr, *part = nullptr, *grad = nullptr,
-        *sq = nullptr, *stats = nullptr, *astats = nullptr;
+  // dXb: the stream gradient in bf16 at a layer's output, dXm after its MLP.
+  uint16_t *ucls = nullptr, *dlog = nullptr, *ducls = nullptr, *dXb = nullptr, *dXm = nullptr,
+           *du = nullptr, *dh = nullptr, *dout = nullptr, *dqkv = nullptr, *WT = nullptr;
+  // Transposed matrices in WT: per layer (wt_stride) W2^T [m][D], W1^T [D][up8(m)],
+  // WO^T [64h][D], WQKV^T [D][192h]; then the classifier's [D][ldlog].
+  int64_t wt_stride = 0, wt_w1 = 0, wt_wo = 0, wt_qkv = 0, wt_head = 0;
+  float *logits = nullptr, *rowloss = nullptr, *dX = nullptr, *part = nullptr, *bpart = nullptr,
+        *grad = nullptr, *sq = nullptr, *stats = nullptr, *astats = nullptr;
+  int bstride = 0;
   int64_t part_floats = 0;
   int ldlog = 0, ldlogits = 0;
   std::vector<ModePlan> plans;  // per k < num_modes - 1 (empty layers when not growable)
@@ -123,18 +132,24 @@ elasto_status_t elasto_growth_create(elasto_handle_t h, int32_t max_batch, elast
   g->max_batch = max_batch;
   const int L = c.depth, D = c.dim, Mh = c.mlp_hidden, C = c.num_classes, T = h->dims.T;
   g->Mmax = (int64_t)max_batch * T;
-  g->Mp8 = up8(g->Mmax);
   const int64_t M = g->Mmax, B = max_batch;
   g->ldlog = (int)up8(C);
   g->ldlogits = (int)up4(C);
 
   // Per-mode plans: gradient arena offsets and update slices.
   std::vector<std::vector<GrowthSlice>> host_slices;
-  int64_t grad_max = 0, slice_max = 0;
+  std::vector<std::vector<TransposeJob>> host_jobs;
+  int64_t grad_max = 0, tiles_max = 0;
+  g->wt_w1 = (int64_t)Mh * D;
+  g->wt_wo = g->wt_w1 + (int64_t)D * up8(Mh);
+  g->wt_qkv = g->wt_wo + (int64_t)D * D;
+  g->wt_stride = g->wt_qkv + 3LL * D * D;
+  g->wt_head = g->wt_stride * L;
   g->plans.resize(h->num_modes > 1 ? h->num_modes - 1 : 0);
   for (int k = 0; k + 1 < h->num_modes; ++k) {
     ModePlan& mp = g->plans[k];
     std::vector<GrowthSlice> sl;
+    std::vector<TransposeJob> jobs;
     const char* why = nullptr;
     if (growable(h, k, &why)) {
       int64_t off = 0;
@@ -152,7 +167,16 @@ elasto_status_t elasto_growth_create(elasto_handle_t h, int32_t max_batch, elast
         lp.fc1b = off; off += dm;
         lp.fc2w = off; off += (int64_t)D * dm;
         mp.layers.push_back(lp);
-        slice_max = std::max(slice_max, std::max(dq * D, dm * D));
+        tiles_max = std::max(tiles_max, 2 * wgrad_tiles((int)dm, D) + wgrad_tiles((int)dq, D) +
+                                            wgrad_tiles(D, 64 * (lp.h - lp.hp)));
+        auto job = [&](int id, int64_t out, int ldi, int ldo, int rows, int cols) {
+          jobs.push_back(TransposeJob{h->lay.get(id, l).offset / 2, g->wt_stride * l + out, ldi, ldo,
+                                      rows, cols});
+        };
+        job(ELASTO_T_W2, 0, Mh, D, D, lp.m);
+        job(ELASTO_T_W1, g->wt_w1, D, (int)up8(lp.m), lp.m, D);
+        job(ELASTO_T_WO, g->wt_wo, D, D, D, 64 * lp.h);
+        job(ELASTO_T_WQKV, g->wt_qkv, D, 192 * lp.h, 192 * lp.h, D);
         auto add = [&](int id, int64_t origin_bytes, int64_t ld, int rows, int cols, int64_t goff,
                        int gld, int bf) {
           if (rows <= 0 || cols <= 0) return;
@@ -170,14 +194,19 @@ elasto_status_t elasto_growth_create(elasto_handle_t h, int32_t max_batch, elast
       }
       mp.grad_floats = off;
       grad_max = std::max(grad_max, off);
+      jobs.push_back(TransposeJob{h->lay.get(ELASTO_T_HEAD_W, 0).offset / 2, g->wt_head, D, g->ldlog,
+                                  C, D});
+      for (const TransposeJob& j : jobs)
+        mp.job_tiles = std::max(mp.job_tiles, (j.rows + 63) / 64 * ((j.cols + 63) / 64));
     }
+    mp.njobs = (int)jobs.size();
+    host_jobs.push_back(std::move(jobs));
     mp.nslices = (int)sl.size();
     host_slices.push_back(std::move(sl));
   }
-  // Split-K partials: up to kMaxSplit chunks of the largest slice.
-  const int kMaxSplit = 32;
-  g->part_floats = kMaxSplit * std::max<int64_t>(up4(std::max(3 * D, Mh)) * D, 1);
-  (void)slice_max;
+  // Split tiles of a layer's weight gradients.
+  g->part_floats = std::max<int64_t>(kWgradSlots, tiles_max) * 128 * 128;
+  g->bstride = std::max(3 * D, Mh);
 
   // One device block for everything.
   const int64_t MD = M * D * 2;
@@ -190,14 +219,15 @@ elasto_status_t elasto_growth_create(elasto_handle_t h, int32_t max_batch, elast
   const size_t i_ucls = want(B * D * 2), i_logits = want(B * g->ldlogits * 4),
                i_dlog = want(B * g->ldlog * 2), i_ducls = want(B * D * 2), i_rowloss = want(B * 4),
                i_dX = want(M * D * 4), i_dXb = want(MD), i_du = want(MD), i_dh = want(M * Mh * 2),
-               i_dout = want(MD), i_dqkv = want(M * 3 * D * 2), i_TA = want(D * g->Mp8 * 2),
-               i_TB = want((int64_t)std::max(Mh, 3 * D) * g->Mp8 * 2),
-               i_WT = want((int64_t)std::max(3 * D, Mh) * D * 2), i_WhT = want((int64_t)D * g->ldlog * 2),
-               i_part = want(g->part_floats * 4), i_grad = want(grad_max * 4),
+               i_dXm = want(MD), i_dout = want(MD), i_dqkv = want(M * 3 * D * 2),
+               i_WT = want((g->wt_head + (int64_t)D * g->ldlog) * 2),
+               i_part = want(g->part_floats * 4),
+               i_bpart = want((int64_t)kWgradMaxSplit * kWgradMax * g->bstride * 4), i_grad = want(grad_max * 4),
                i_sq = want((int64_t)growth_sumsq_parts() * 4), i_stats = want(4 * 4),
                i_astats = want((int64_t)B * h->cfg.heads * T * 2 * 4);
   int64_t slice_bytes = 0;
   for (const auto& v : host_slices) slice_bytes += al256((int64_t)v.size() * sizeof(GrowthSlice));
+  for (const auto& v : host_jobs) slice_bytes += al256((int64_t)v.size() * sizeof(TransposeJob));
   const size_t i_slices = want(slice_bytes);
   int64_t total = 0;
   std::vector<int64_t> offs(sizes.size());
@@ -229,8 +259,8 @@ elasto_status_t elasto_growth_create(elasto_handle_t h, int32_t max_batch, elast
   }
   g->ucls = bf(i_ucls); g->logits = fl(i_logits); g->dlog = bf(i_dlog); g->ducls = bf(i_ducls);
   g->rowloss = fl(i_rowloss); g->dX = fl(i_dX); g->dXb = bf(i_dXb); g->du = bf(i_du);
-  g->dh = bf(i_dh); g->dout = bf(i_dout); g->dqkv = bf(i_dqkv); g->TA = bf(i_TA); g->TB = bf(i_TB);
-  g->WT = bf(i_WT); g->WhT = bf(i_WhT); g->part = fl(i_part); g->grad = fl(i_grad);
+  g->dh = bf(i_dh); g->dXm = bf(i_dXm); g->dout = bf(i_dout); g->dqkv = bf(i_dqkv);
+  g->WT = bf(i_WT); g->part = fl(i_part); g->bpart = fl(i_bpart); g->grad = fl(i_grad);
   g->sq = fl(i_sq); g->stats = fl(i_stats); g->astats = fl(i_astats);
 
   hipError_t e = hipSuccess;
@@ -239,6 +269,12 @@ elasto_status_t elasto_growth_create(elasto_handle_t h, int32_t max_batch, elast
     g->plans[k].slices = reinterpret_cast<GrowthSlice*>(sp);
     const int64_t bytes = (int64_t)host_slices[k].size() * sizeof(GrowthSlice);
     if (bytes > 0) e = hipMemcpy(sp, host_slices[k].data(), (size_t)bytes, hipMemcpyHostToDevice);
+    sp += al256(bytes);
+  }
+  for (size_t k = 0; k < host_jobs.size() && e == hipSuccess; ++k) {
+    g->plans[k].jobs = reinterpret_cast<TransposeJob*>(sp);
+    const int64_t bytes = (int64_t)host_jobs[k].size() * sizeof(TransposeJob);
+    if (bytes > 0) e = hipMemcpy(sp, host_jobs[k].data(), (size_t)bytes, hipMemcpyHostToDevice);
     sp += al256(bytes);
   }
   // Masters of the re-trainable matrices.
@@ -307,7 +343,7 @@ elasto_status_t elasto_growth_step(elasto_growth_t g, int32_t mode, const void* 
   const elasto_config_t& c = h->cfg;
   const Dims& d = h->dims;
   const int L = c.depth, D = c.dim, Mh = c.mlp_hidden, C = c.num_classes, T = d.T;
-  const int64_t M = (int64_t)batch * T, Mp8 = g->Mp8;
+  const int64_t M = (int64_t)batch * T;
   const ModePlan& plan = g->plans[mode];
   const float scale = 1.0f / sqrtf((float)d.hd);
   hipError_t e = hipSuccess;
@@ -324,27 +360,6 @@ elasto_status_t elasto_growth_step(elasto_growth_t g, int32_t mode, const void* 
     a.M = rows; a.N = N; a.K = K;
     return a;
   };
-  // Weight gradient out[r][c] = sum_m At[r][m] * Bt[c][m] (At: ra rows, Bt: rb
-  // rows, both [.][Mp8] bf16) into the gradient arena (row stride rb).
-  auto wgrad = [&](const uint16_t* At, int ra, const uint16_t* Bt, int rb, float* outp) {
-    if (ra <= 0 || rb <= 0) return hipSuccess;
-    const int64_t tiles = ((ra + 255) / 256) * (int64_t)((rb + 255) / 256);
-    const int64_t ksteps = (M + 63) / 64;
-    int split = (int)std::min<int64_t>({32, std::max<int64_t>(1, 512 / tiles), std::max<int64_t>(1, ksteps / 4)});
-    const int64_t kchunk = ((ksteps + split - 1) / split) * 64;
-    split = (int)((M + kchunk - 1) / kchunk);
-    const int64_t ldp = up4(rb);
-    GemmArgs a = gemm(Epi::BiasF32, At, Mp8, Bt, Mp8, g->part, ldp, nullptr, ra, rb, (int)M);
-    a.ksplit = split;
-    a.kchunk = (int)kchunk;
-    a.c_split = (int64_t)ra * ldp;
-    if (split > 1 && a.c_split * split > g->part_floats) return hipErrorInvalidValue;
-    if (split == 1) a.ksplit = 1;
-    hipError_t r = launch_gemm_bf16(Epi::BiasF32, a, s);
-    if (r != hipSuccess) return r;
-    return launch_splitk_reduce(g->part, a.c_split, split, ra, rb, ldp, outp, rb, s);
-  };
-
   // ------------------------------------------------------------ forward
   {
     GemmArgs a = gemm(Epi::Patch, nullptr, 0, Wb(h, ELASTO_T_PATCH_W), d.patch_k, g->X[0], D,
@@ -394,9 +409,10 @@ elasto_status_t elasto_growth_step(elasto_growth_t g, int32_t mode, const void* 
   // ------------------------------------------------------------ backward
   G_TRY(launch_cross_entropy(g->logits, g->ldlogits, labels, C, batch, g->dlog, g->ldlog,
                              g->rowloss, s), "cross-entropy");
-  G_TRY(launch_transpose_bf16(Wb(h, ELASTO_T_HEAD_W), D, 0, C, D, g->WhT, g->ldlog, s), "head^T");
-  G_TRY(launch_gemm_bf16(Epi::Bias, gemm(Epi::Bias, g->dlog, g->ldlog, g->WhT, g->ldlog, g->ducls, D,
-                                         nullptr, batch, D, C), s), "head backward");
+  G_TRY(launch_transposes_bf16(plan.jobs, plan.njobs, plan.job_tiles, h->dw, g->WT, s),
+        "weight transposes");
+  G_TRY(launch_gemm_bf16(Epi::Bias, gemm(Epi::Bias, g->dlog, g->ldlog, g->WT + g->wt_head, g->ldlog,
+                                         g->ducls, D, nullptr, batch, D, C), s), "head backward");
   G_TRY(hipMemsetAsync(g->dX, 0, (size_t)(M * D * 4), s), "clear dX");
   G_TRY(hipMemsetAsync(g->dXb, 0, (size_t)(M * D * 2), s), "clear dX bf16");
   G_TRY(launch_layernorm_bwd_bf16(g->X[L], (int64_t)T * D, g->ducls, D, Fp(h, ELASTO_T_NORM_G),
@@ -405,39 +421,21 @@ elasto_status_t elasto_growth_step(elasto_growth_t g, int32_t mode, const void* 
   for (int l = L - 1; l >= 0; --l) {
     const LayerPlan& lp = plan.layers[l];
     const int dm = lp.m - lp.mp, dhd = lp.h - lp.hp;
+    const uint16_t* wt = g->WT + g->wt_stride * l;
     // fc2
-    G_TRY(launch_transpose_bf16(Wb(h, ELASTO_T_W2, l), Mh, 0, D, lp.m, g->WT, D, s), "W2^T %d", l);
     {
-      GemmArgs a = gemm(Epi::GeluBwd, g->dXb, D, g->WT, D, g->dh, Mh, nullptr, M, lp.m, D);
+      GemmArgs a = gemm(Epi::GeluBwd, g->dXb, D, wt, D, g->dh, Mh, nullptr, M, lp.m, D);
       a.aux = g->pre[l]; a.ldaux = Mh;
       G_TRY(launch_gemm_bf16(Epi::GeluBwd, a, s), "fc2 backward %d", l);
     }
-    if (dm > 0) {
-      G_TRY(launch_transpose_bf16(g->dXb, D, 0, (int)M, D, g->TA, Mp8, s), "dX^T %d", l);
-      G_TRY(launch_transpose_bf16(g->gact[l], Mh, lp.mp, (int)M, dm, g->TB, Mp8, s), "g^T %d", l);
-      G_TRY(wgrad(g->TA, D, g->TB, dm, g->grad + lp.fc2w), "dW2 %d", l);
-    }
     // fc1
-    G_TRY(launch_transpose_bf16(Wb(h, ELASTO_T_W1, l), D, 0, lp.m, D, g->WT, up8(lp.m), s), "W1^T %d", l);
-    G_TRY(launch_gemm_bf16(Epi::Bias, gemm(Epi::Bias, g->dh, Mh, g->WT, up8(lp.m), g->du, D, nullptr,
-                                           M, D, lp.m), s), "fc1 backward %d", l);
-    if (dm > 0) {
-      G_TRY(launch_transpose_bf16(g->dh, Mh, lp.mp, (int)M, dm, g->TB, Mp8, s), "dh^T %d", l);
-      G_TRY(launch_transpose_bf16(g->u2[l], D, 0, (int)M, D, g->TA, Mp8, s), "u2^T %d", l);
-      G_TRY(wgrad(g->TB, dm, g->TA, D, g->grad + lp.fc1w), "dW1 %d", l);
-      G_TRY(launch_rowsum_bf16(g->TB, Mp8, dm, (int)M, g->grad + lp.fc1b, s), "db1 %d", l);
-    }
+    G_TRY(launch_gemm_bf16(Epi::Bias, gemm(Epi::Bias, g->dh, Mh, wt + g->wt_w1, up8(lp.m), g->du, D,
+                                           nullptr, M, D, lp.m), s), "fc1 backward %d", l);
     G_TRY(launch_layernorm_bwd_bf16(g->Xm[l], D, g->du, D, Fp(h, ELASTO_T_LN2_G, l), c.ln_eps,
-                                    (int)M, D, g->dX, D, g->dXb, D, s), "ln2 backward %d", l);
+                                    (int)M, D, g->dX, D, g->dXm, D, s), "ln2 backward %d", l);
     // proj
-    G_TRY(launch_transpose_bf16(Wb(h, ELASTO_T_WO, l), D, 0, D, 64 * lp.h, g->WT, D, s), "WO^T %d", l);
-    G_TRY(launch_gemm_bf16(Epi::Bias, gemm(Epi::Bias, g->dXb, D, g->WT, D, g->dout, D, nullptr, M,
-                                           64 * lp.h, D), s), "proj backward %d", l);
-    if (dhd > 0) {
-      G_TRY(launch_transpose_bf16(g->dXb, D, 0, (int)M, D, g->TA, Mp8, s), "dX^T %d", l);
-      G_TRY(launch_transpose_bf16(g->o[l], D, 64 * lp.hp, (int)M, 64 * dhd, g->TB, Mp8, s), "o^T %d", l);
-      G_TRY(wgrad(g->TA, D, g->TB, 64 * dhd, g->grad + lp.proj), "dWO %d", l);
-    }
+    G_TRY(launch_gemm_bf16(Epi::Bias, gemm(Epi::Bias, g->dXm, D, wt + g->wt_wo, D, g->dout, D,
+                                           nullptr, M, 64 * lp.h, D), s), "proj backward %d", l);
     // attention
     {
       AttnBwdArgs ab;
@@ -447,16 +445,19 @@ elasto_status_t elasto_growth_step(elasto_growth_t g, int32_t mode, const void* 
       G_TRY(launch_attention_bwd_bf16(ab, s), "attention backward %d", l);
     }
     // qkv
-    G_TRY(launch_transpose_bf16(Wb(h, ELASTO_T_WQKV, l), D, 0, 192 * lp.h, D, g->WT, 192 * lp.h, s),
-          "WQKV^T %d", l);
-    G_TRY(launch_gemm_bf16(Epi::Bias, gemm(Epi::Bias, g->dqkv, 3 * D, g->WT, 192 * lp.h, g->du, D,
-                                           nullptr, M, D, 192 * lp.h), s), "qkv backward %d", l);
-    if (dhd > 0) {
-      G_TRY(launch_transpose_bf16(g->dqkv, 3 * D, 192 * lp.hp, (int)M, 192 * dhd, g->TB, Mp8, s),
-            "dqkv^T %d", l);
-      G_TRY(launch_transpose_bf16(g->u1[l], D, 0, (int)M, D, g->TA, Mp8, s), "u1^T %d", l);
-      G_TRY(wgrad(g->TB, 192 * dhd, g->TA, D, g->grad + lp.qkvw), "dWQKV %d", l);
-      G_TRY(launch_rowsum_bf16(g->TB, Mp8, 192 * dhd, (int)M, g->grad + lp.qkvb, s), "dbqkv %d", l);
+    G_TRY(launch_gemm_bf16(Epi::Bias, gemm(Epi::Bias, g->dqkv, 3 * D, wt + g->wt_qkv, 192 * lp.h,
+                                           g->du, D, nullptr, M, D, 192 * lp.h), s),
+          "qkv backward %d", l);
+    // Gradients of the re-introduced slices.
+    {
+      float* gr = g->grad;
+      const WgradArgs w[4] = {
+          {g->dXb, g->gact[l], D, Mh, 0, lp.mp, dm > 0 ? D : 0, dm, gr + lp.fc2w, nullptr},
+          {g->dh, g->u2[l], Mh, D, lp.mp, 0, dm, D, gr + lp.fc1w, gr + lp.fc1b},
+          {g->dXm, g->o[l], D, D, 0, 64 * lp.hp, dhd > 0 ? D : 0, 64 * dhd, gr + lp.proj, nullptr},
+          {g->dqkv, g->u1[l], 3 * D, D, 192 * lp.hp, 0, 192 * dhd, D, gr + lp.qkvw, gr + lp.qkvb}};
+      G_TRY(launch_wgrad_bf16(w, 4, M, g->part, g->part_floats, g->bpart, g->bstride, s),
+            "weight gradients %d", l);
     }
     G_TRY(launch_layernorm_bwd_bf16(g->X[l], D, g->du, D, Fp(h, ELASTO_T_LN1_G, l), c.ln_eps,
                                     (int)M, D, g->dX, D, g->dXb, D, s), "ln1 backward %d", l);

@@ -175,9 +175,29 @@ struct AttnBwdArgs {
 hipError_t launch_attention_bwd_bf16(const AttnBwdArgs& a, hipStream_t s);
 
 // Growth-step helpers (growth_kernels.hip).
-// out[c][r] = in[r][c0 + c], r < rows, c < n (bf16; ldo % 8 == 0, ldo >= rows).
-hipError_t launch_transpose_bf16(const void* in, int64_t ldi, int64_t c0, int rows, int n,
-                                 void* out, int64_t ldo, hipStream_t s);
+// out[c][r] = in[r][c], r < rows, c < cols, of every job in one launch (bf16;
+// offsets in elements from the launch's in / out, multiples of 8; ldi and ldo
+// multiples of 8).  jobs: device array; max_tiles: the most 64x64 tiles of a job.
+struct TransposeJob {
+  int64_t in_off, out_off;
+  int32_t ldi, ldo, rows, cols;
+};
+hipError_t launch_transposes_bf16(const TransposeJob* jobs, int njobs, int max_tiles, const void* in,
+                                  void* out, hipStream_t s);
+// Weight gradients of up to kWgradMax linear layers over the same M rows:
+// out[r][c] = sum_m P[m][pc + r] Q[m][qc + c], r < ra, c < rb (bf16 in, fp32
+// out, row stride rb) and, where bias is given, bias[r] = sum_m P[m][pc + r].
+// part holds part_floats floats of scratch, bpart kWgradMaxSplit * kWgradMax *
+// bstride (bstride >= every ra).
+struct WgradArgs {
+  const void *P, *Q;
+  int32_t ldp, ldq, pc, qc, ra, rb;
+  float *out, *bias;
+};
+constexpr int kWgradMax = 4, kWgradSlots = 512, kWgradMaxSplit = 32;
+int64_t wgrad_tiles(int ra, int rb);  // tiles of 128 x 128 fp32 partials a problem takes at most
+hipError_t launch_wgrad_bf16(const WgradArgs* probs, int n, int64_t M, float* part,
+                             int64_t part_floats, float* bpart, int bstride, hipStream_t s);
 // LayerNorm backward (gamma only; beta and gamma are not trained): from x
 // (the LN input, bf16) and dy (bf16), dX[r] += dx (fp32) and dXb[r] = bf16(dX[r]).
 hipError_t launch_layernorm_bwd_bf16(const void* x, int64_t ldx, const void* dy, int64_t ldy,
@@ -188,10 +208,6 @@ hipError_t launch_layernorm_bwd_bf16(const void* x, int64_t ldx, const void* dy,
 hipError_t launch_cross_entropy(const float* logits, int64_t ldl, const int32_t* labels, int C,
                                 int batch, void* dlogits, int64_t ldd, float* rowloss,
                                 hipStream_t s);
-hipError_t launch_rowsum_bf16(const void* in, int64_t ld, int rows, int n, float* out,
-                              hipStream_t s);
-hipError_t launch_splitk_reduce(const float* part, int64_t c_split, int ksplit, int rows, int cols,
-                                int64_t ldp, float* out, int64_t ldo, hipStream_t s);
 // stats[0..2] = mean loss, L2 norm of grad[0, n), clip factor min(1, clip / norm);
 // part holds growth_sumsq_parts() floats of scratch.
 int growth_sumsq_parts();

@@ -155,8 +155,14 @@ hipError_t launch_layernorm_f32(const void*, int64_t, void*, int64_t, int, const
 hipError_t launch_attention_bf16(const AttnArgs&, hipStream_t) { return launch(); }
 hipError_t launch_attention_f32(const AttnArgs&, hipStream_t) { return launch(); }
 hipError_t launch_attention_bwd_bf16(const AttnBwdArgs&, hipStream_t) { return launch(); }
-hipError_t launch_transpose_bf16(const void*, int64_t, int64_t, int, int, void*, int64_t,
-                                 hipStream_t) {
+hipError_t launch_transposes_bf16(const TransposeJob*, int, int, const void*, void*, hipStream_t) {
+  return launch();
+}
+int64_t wgrad_tiles(int ra, int rb) {
+  return (int64_t)((ra + 7 + 127) / 128) * ((rb + 7 + 127) / 128);
+}
+hipError_t launch_wgrad_bf16(const WgradArgs*, int, int64_t, float*, int64_t, float*, int,
+                             hipStream_t) {
   return launch();
 }
 hipError_t launch_layernorm_bwd_bf16(const void*, int64_t, const void*, int64_t, const float*,
@@ -166,13 +172,6 @@ hipError_t launch_layernorm_bwd_bf16(const void*, int64_t, const void*, int64_t,
 }
 hipError_t launch_cross_entropy(const float*, int64_t, const int32_t*, int, int, void*, int64_t,
                                 float*, hipStream_t) {
-  return launch();
-}
-hipError_t launch_rowsum_bf16(const void*, int64_t, int, int, float*, hipStream_t) {
-  return launch();
-}
-hipError_t launch_splitk_reduce(const float*, int64_t, int, int, int, int64_t, float*, int64_t,
-                                hipStream_t) {
   return launch();
 }
 int growth_sumsq_parts() { return 64; }
