@@ -579,6 +579,7 @@ elasto_status_t cnn_run(elasto_cnn_t h, const void* images, int32_t batch, float
   auto gemm = [&](Epi epi, const void* A, int64_t lda, int64_t wo, int64_t ldw, void* C, int64_t ldc,
                   int64_t bo, int64_t M, int N, int K, bool relu, int plan) {
     GemmArgs a;
+    a.one_order = true;
     a.A = A; a.lda = lda;
     a.W = Wp(wo); a.ldw = ldw;
     a.C = C; a.ldc = ldc;

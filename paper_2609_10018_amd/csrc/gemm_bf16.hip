@@ -73,6 +73,7 @@ struct Params {
   int group_m;  // row panels per rasterisation group
   int relu;     // Bias / BiasResid: clamp the bf16 result at 0 (convolution blocks)
   int plan;     // forced tile plan (GemmArgs::plan), 0: the planner
+  int one_order;  // GemmArgs::one_order
   // Implicit convolution: input [*, H, W, Cs] (first Ca channels active),
   // KH x KW taps (row-major), stride, zero padding, output Ho x Wo; weights
   // stride wseg elements per tap; nc = 64-channel steps per tap; buffer
@@ -288,10 +289,13 @@ __device__ __forceinline__ u32x4 mask_tail(u32x4 v, int kbeg, int kend) {
 // STAGES: LDS stages of the tile loads (2: the next K step in flight while
 // this one computes; 4: three steps in flight, for launches of few tiles whose
 // K chain is bound by the load latency; needs K % 64 == 0 and no CONV).
-template <int BM, int BN, int WM, int WN, Epi E, bool CONV, int STAGES = 2>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(Params p) {
+// KS: groups of WM x WN waves that share out the four 16-value quarters of every
+// step; the groups' sums are added in LDS before the epilogue.
+template <int BM, int BN, int WM, int WN, Epi E, bool CONV, int STAGES = 2, int KS = 1>
+__global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(Params p) {
   static_assert(STAGES == 2 || (STAGES == 4 && !CONV), "stage counts");
-  constexpr int NW = WM * WN;
+  static_assert(KS == 1 || (KS == 2 && !CONV && E != Epi::Patch && BM <= 128), "K groups");
+  constexpr int NW = WM * WN * KS;
   constexpr int WTM = BM / WM, WTN = BN / WN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
   constexpr int ABLK = BM / kRowsPerBlock, BBLK = BN / kRowsPerBlock;
@@ -327,7 +331,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(Params p) {
       p.C = static_cast<float*>(p.C) + blockIdx.y * p.c_split;
     }
   }
-  const int wm = wave / WN, wn = wave % WN;
+  const int kg = KS == 1 ? 0 : wave / (WM * WN), wave_g = KS == 1 ? wave : wave % (WM * WN);
+  const int wm = wave_g / WN, wn = wave_g % WN;
 
   // Tile order: workgroup i runs on XCD i % 8, so each XCD first receives a
   // contiguous run of logical tile ids; logical ids then walk groups of
@@ -579,8 +584,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(Params p) {
     }
     const char* cur = smem + (STAGES == 2 ? (kt & 1) : (kt % STAGES)) * STAGE;
 #pragma unroll
-    for (int kk = 0; kk < kBK / 16; ++kk) {
-      const int c = kk * 2 + lg;
+    for (int k4 = 0; k4 < kBK / 16 / KS; ++k4) {
+      const int c = (kg * (kBK / 16 / KS) + k4) * 2 + lg;
       bf16x8 af[TM], bf[TN];
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
@@ -669,7 +674,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(Params p) {
                       : u32x4{0u, 0u, 0u, 0u};
       }
     }
-    if ((wm * WTM) / SR == pass) {
+    if ((wm * WTM) / SR == pass && kg == KS - 1) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -679,6 +684,21 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(Params p) {
             const int rl = (wm * WTM) % SR + i * 32 + 8 * (e >> 2) + 4 * lg + (e & 3);
             stg[rl * SS + wn * WTN + j * 32 + lr] = acc[i][j][e];
           }
+    }
+    if constexpr (KS > 1) {  // group 0 adds its sums to group 1's
+      wait_lds();
+      __builtin_amdgcn_s_barrier();
+      if (kg == 0) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              const int rl = wm * WTM + i * 32 + 8 * (e >> 2) + 4 * lg + (e & 3);
+              stg[rl * SS + wn * WTN + j * 32 + lr] += acc[i][j][e];
+            }
+      }
     }
     wait_lds();
     __builtin_amdgcn_s_barrier();
@@ -1535,7 +1555,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_small(Params p) {
   }
 }
 
-template <int BM, int BN, int WM, int WN, Epi E, bool CONV, int STAGES = 2>
+template <int BM, int BN, int WM, int WN, Epi E, bool CONV, int STAGES = 2, int KS = 1>
 hipError_t launch_cfg(const Params& p0, int row0, hipStream_t s) {
   Params p = p0;
   p.row0 = row0;
@@ -1547,9 +1567,9 @@ hipError_t launch_cfg(const Params& p0, int row0, hipStream_t s) {
   const int64_t blocks = tm * tn;
   if (blocks <= 0) return hipSuccess;
   const bool ln_consumer = (E == Epi::Bias || E == Epi::BiasGelu) && !CONV && p.ln_in != nullptr;
-  hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, CONV, STAGES>),
+  hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E, CONV, STAGES, KS>),
                      dim3((unsigned)blocks, (unsigned)(p.ksplit > 1 ? p.ksplit : 1)),
-                     dim3(64 * WM * WN), ln_consumer ? BM * 8 : 0, s, p);
+                     dim3(64 * WM * WN * KS), ln_consumer ? BM * 8 : 0, s, p);
   return hipGetLastError();
 }
 
@@ -1745,11 +1765,19 @@ hipError_t launch_epi(const Params& p, hipStream_t s) {
     case 1: return launch_cfg<256, 128, 2, 2, E, CONV>(p, 0, s);
     case 2:
       // Less than a round of tiles: each workgroup's K chain is the critical
-      // path, so keep three steps of loads in flight.
-      if constexpr (!CONV && (E == Epi::Bias || E == Epi::BiasGelu || E == Epi::BiasResid)) {
+      // path, so keep three steps of loads in flight and let two groups of
+      // four waves halve each step (a second wave per SIMD to fill the waits:
+      // 3152 x 768 x 3072 36.2 -> 30.3 us, 7289 x 384 x 691 14.5 -> 12.3; with
+      // one group and four stages only where K % 64 == 0).  The groups' sums
+      // are in another order than the other plans': not for one_order.
+      if constexpr (!CONV && E != Epi::Patch) {
         const int64_t tiles = ((p.M + 127) / 128) * ((p.N + 127) / 128);
-        if (tiles < kCUs && p.K % kBK == 0 && p.K / kBK >= 4)
-          return launch_cfg<128, 128, 2, 2, E, CONV, 4>(p, 0, s);
+        if (tiles < kCUs && p.ksplit <= 1 && !p.one_order)
+          return launch_cfg<128, 128, 2, 2, E, CONV, 4, 2>(p, 0, s);
+        if constexpr (E == Epi::Bias || E == Epi::BiasGelu || E == Epi::BiasResid) {
+          if (tiles < kCUs && p.K % kBK == 0 && p.K / kBK >= 4)
+            return launch_cfg<128, 128, 2, 2, E, CONV, 4>(p, 0, s);
+        }
       }
       return launch_cfg<128, 128, 2, 2, E, CONV>(p, 0, s);
     default: return launch_cfg<256, 64, 4, 1, E, CONV>(p, 0, s);
@@ -1867,6 +1895,7 @@ hipError_t launch_gemm_bf16(Epi epi, const GemmArgs& a, hipStream_t s) {
   p.ccls = a.ccls;
   p.relu = a.relu ? 1 : 0;
   p.plan = a.plan;
+  p.one_order = a.one_order ? 1 : 0;
   p.res = static_cast<const uint16_t*>(a.res);
   p.ldres = a.ldres;
   p.aux = static_cast<uint16_t*>(a.aux);

@@ -82,6 +82,9 @@ struct GemmArgs {
   // runs that one configuration, or returns hipErrorNotSupported where it
   // cannot take these arguments.
   int plan = 0;
+  // Tiled launches of plan 0 sum K in the one order of plans 1-6 (the CNN: its
+  // outputs then do not depend on which tile plan the tuning chose).
+  bool one_order = false;
 };
 
 // Tile plans a caller may force (GemmArgs::plan, ConvArgs::plan): 1 256x256,
@@ -93,7 +96,9 @@ struct GemmArgs {
 // class-token rows (ccls) the outputs are bit-identical whatever the plan.
 // Plan 0 takes the kernel of gemm_small.h for launches whose 64x64 tiles (or
 // smaller ones) all run at once; its sums are split over four waves, so its
-// bits differ from the other plans', but not with the launch's size.
+// bits differ from the other plans', but not with the launch's size.  Without
+// one_order it also splits the steps of 128x128 tiles that fill less than a
+// round over two groups of waves.
 // Plans kSplitPlan0 + i split K into about kSplitChunks[i] chunks (bf16 Bias /
 // BiasGelu / BiasResid with a workspace, where the 128x128 tiles would fill
 // under half the CUs and plan 0 has no one-round kernel; the partials are

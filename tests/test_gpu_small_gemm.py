@@ -132,3 +132,13 @@ def test_small_linear_f32(epi, M, N, K, lda):
     scale = float(z.abs().max()) + K ** 0.5
     assert float((c[:, :N].double() - z).abs().max()) < scale * 2.0 ** -20
     assert torch.equal(c[:, N], c0[:, N])
+
+
+@pytest.mark.parametrize("M,N,K,ld", [(3000, 700, 40, 40), (3000, 700, 64, 64), (2500, 1000, 130, 136),
+                                      (2050, 1030, 333, 336), (7289, 384, 691, 1536),
+                                      (1576, 768, 1536, 1536)])
+@pytest.mark.parametrize("epi", [ffi.EPI_BIAS, ffi.EPI_BIAS_GELU, ffi.EPI_BIAS_RESID,
+                                 ffi.EPI_BIAS_F32OUT])
+def test_linear_in_less_than_a_round_of_128_tiles(epi, M, N, K, ld):
+    """Too large for 64x64 tiles in one round, fewer 128x128 tiles than CUs."""
+    test_small_linear(epi, M, N, K, ld, ld)
