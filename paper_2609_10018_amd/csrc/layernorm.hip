@@ -13,6 +13,7 @@ namespace elasto {
 namespace {
 
 constexpr int kMaxChunks = 8;  // 8-element chunks per lane: d <= 2048
+constexpr int kLnGroups = 1280;  // workgroups that walk rows: five on each of 256 CUs
 
 __device__ __forceinline__ float half_sum(float v) {
 #pragma unroll
@@ -21,89 +22,145 @@ __device__ __forceinline__ float half_sum(float v) {
 }
 
 // Two rows per wave (32 lanes each), so a load instruction moves 16 bytes per
-// lane; NC = ceil(d / 256) chunks per lane.  Rows past the end re-read the
-// last row and store nothing.
-template <int NC>
+// lane; NC = ceil(d / 256) chunks per lane.
+//
+// Bound by HBM and the last-level cache.  A chunk's load was behind the test
+// for a class-token row, so the row's loads waited for one another: 36.3 us for
+// 50432 x 768; with the loads ahead of the test 25.6.  Rows that fill the chip
+// more than once (WALK): a half-wave walks rows `step` apart, the next row's
+// load in flight under the current row's sums, with g and b, four times a row's
+// bytes, staged in LDS once: 25.1 us, 25000 x 768 15.0 -> 13.1, 50432 x 384
+// 15.0 -> 13.4 (768 to 2048 workgroups: 24.9 to 27.6; 1280 is best or within
+// 2%).  Not for d > 1024, where the registers of a row ahead cost wavefronts
+// (50432 x 2048: 84.4 against 81.4).
+// step = step_q * tokens + step_r, so a row's image needs no division.
+struct LnRows {
+  int64_t step, step_q;
+  int step_r;
+};
+
+template <int NC, bool WALK>
 __global__ __launch_bounds__(256) void layernorm_bf16_kernel(const uint16_t* __restrict__ x,
                                                              int64_t x_stride,
                                                              const float* __restrict__ xcls,
-                                                             int tokens,
+                                                             int tokens, LnRows walk,
                                                              uint16_t* __restrict__ out,
                                                              int64_t rows, int d,
                                                              const float* __restrict__ g,
                                                              const float* __restrict__ b,
                                                              float eps) {
-  const int hl = threadIdx.x & 31;
-  const int64_t row_raw = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
-  const bool live = row_raw < rows;
-  const int64_t row = live ? row_raw : rows - 1;
-  const int nch = d >> 3;
-  const int64_t bi = xcls != nullptr ? row / tokens : 0;
-  const bool cls_row = xcls != nullptr && row == bi * tokens;  // uniform per half-wave
-  const uint16_t* xr = x + row * x_stride;
-  const float* xc = cls_row ? xcls + bi * (int64_t)d : nullptr;
-  float v[NC][8];
-  float s = 0.0f;
-#pragma unroll
-  for (int i = 0; i < NC; ++i) {
-    const int ci = hl + 32 * i;
-    if (ci < nch) {
-      if (cls_row) {
-        const f32x4 w0 = *reinterpret_cast<const f32x4*>(xc + 8 * ci);
-        const f32x4 w1 = *reinterpret_cast<const f32x4*>(xc + 8 * ci + 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[i][e] = w0[e];
-          v[i][4 + e] = w1[e];
-        }
-      } else {
-        const u32x4 w = *reinterpret_cast<const u32x4*>(xr + 8 * ci);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[i][2 * e] = __uint_as_float(w[e] << 16);
-          v[i][2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u);
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s += v[i][e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[i][e] = 0.0f;
+  // Half h of chunk ci of g (then of b) at [h][ci]: a wave's reads are contiguous.
+  __shared__ f32x4 gb[WALK ? 4 * NC * 32 : 1];
+  const int nch = d >> 3, hl = threadIdx.x & 31;
+  if constexpr (WALK) {
+    for (int q = threadIdx.x; q < 2 * nch; q += 256) {
+      gb[(q & 1) * NC * 32 + (q >> 1)] = *reinterpret_cast<const f32x4*>(g + 4 * q);
+      gb[(2 + (q & 1)) * NC * 32 + (q >> 1)] = *reinterpret_cast<const f32x4*>(b + 4 * q);
     }
   }
+  int64_t row = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
+  bool live = row < rows;  // the same for a half-wave: the sums below stay inside one
+  int64_t bi = 0;
+  int tok = 1;  // row = bi * tokens + tok; without class rows never 0
+  if (xcls != nullptr) {
+    bi = row / tokens;
+    tok = (int)(row - bi * tokens);
+  }
+  u32x4 raw[NC];
+  auto load_row = [&]() {
+    const uint16_t* xr = x + row * x_stride;
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+      if (hl + 32 * i < nch) raw[i] = *reinterpret_cast<const u32x4*>(xr + 8 * (hl + 32 * i));
+  };
+  if (live && tok != 0) load_row();
+  if constexpr (WALK) __syncthreads();
   const float inv_d = 1.0f / (float)d;
-  const float mean = half_sum(s) * inv_d;
-  float ss = 0.0f;
+  while (live) {
+    float v[NC][8];
+    float s = 0.0f;
 #pragma unroll
-  for (int i = 0; i < NC; ++i) {
-    if (hl + 32 * i < nch) {
+    for (int i = 0; i < NC; ++i) {
+      const int ci = hl + 32 * i;
+      if (ci < nch) {
+        if (tok == 0) {
+          const float* xc = xcls + bi * (int64_t)d;
+          const f32x4 w0 = *reinterpret_cast<const f32x4*>(xc + 8 * ci);
+          const f32x4 w1 = *reinterpret_cast<const f32x4*>(xc + 8 * ci + 4);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float c = v[i][e] - mean;
-        ss += c * c;
+          for (int e = 0; e < 4; ++e) {
+            v[i][e] = w0[e];
+            v[i][4 + e] = w1[e];
+          }
+        } else {
+          const u32x4 w = raw[i];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[i][2 * e] = __uint_as_float(w[e] << 16);
+            v[i][2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u);
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += v[i][e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[i][e] = 0.0f;
       }
     }
-  }
-  const float rstd = rsqrtf(half_sum(ss) * inv_d + eps);
-  if (!live) return;
-  uint16_t* orow = out + row * (int64_t)d;
-#pragma unroll
-  for (int i = 0; i < NC; ++i) {
-    const int ci = hl + 32 * i;
-    if (ci < nch) {
-      const f32x4 g0 = *reinterpret_cast<const f32x4*>(g + 8 * ci);
-      const f32x4 g1 = *reinterpret_cast<const f32x4*>(g + 8 * ci + 4);
-      const f32x4 b0 = *reinterpret_cast<const f32x4*>(b + 8 * ci);
-      const f32x4 b1 = *reinterpret_cast<const f32x4*>(b + 8 * ci + 4);
-      const float gv[8] = {g0[0], g0[1], g0[2], g0[3], g1[0], g1[1], g1[2], g1[3]};
-      const float bv[8] = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
-      u32x4 w;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        w[e] = pack_bf16x2((v[i][2 * e] - mean) * rstd * gv[2 * e] + bv[2 * e],
-                           (v[i][2 * e + 1] - mean) * rstd * gv[2 * e + 1] + bv[2 * e + 1]);
+    uint16_t* orow = out + row * (int64_t)d;
+    if constexpr (WALK) {
+      row += walk.step;
+      live = row < rows;
+      if (xcls != nullptr) {
+        bi += walk.step_q;
+        tok += walk.step_r;
+        if (tok >= tokens) {
+          tok -= tokens;
+          ++bi;
+        }
       }
-      *reinterpret_cast<u32x4*>(orow + 8 * ci) = w;
+      if (live && tok != 0) load_row();
+    } else {
+      live = false;
+    }
+
+    const float mean = half_sum(s) * inv_d;
+    float ss = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      if (hl + 32 * i < nch) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float c = v[i][e] - mean;
+          ss += c * c;
+        }
+      }
+    }
+    const float rstd = rsqrtf(half_sum(ss) * inv_d + eps);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const int ci = hl + 32 * i;
+      if (ci < nch) {
+        u32x4 w;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          f32x4 gv, bv;
+          if constexpr (WALK) {
+            gv = gb[h * NC * 32 + ci];
+            bv = gb[(2 + h) * NC * 32 + ci];
+          } else {
+            gv = *reinterpret_cast<const f32x4*>(g + 8 * ci + 4 * h);
+            bv = *reinterpret_cast<const f32x4*>(b + 8 * ci + 4 * h);
+          }
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const int j = 2 * e;
+            w[2 * h + e] = pack_bf16x2((v[i][4 * h + j] - mean) * rstd * gv[j] + bv[j],
+                                       (v[i][4 * h + j + 1] - mean) * rstd * gv[j + 1] + bv[j + 1]);
+          }
+        }
+        *reinterpret_cast<u32x4*>(orow + 8 * ci) = w;
+      }
     }
   }
 }
@@ -148,8 +205,24 @@ template <int NC>
 hipError_t launch_ln(const uint16_t* x, int64_t x_stride, const float* xcls, int tokens,
                      uint16_t* out, int64_t rows, int d, const float* g, const float* b, float eps,
                      hipStream_t s) {
-  hipLaunchKernelGGL(layernorm_bf16_kernel<NC>, dim3((unsigned)((rows + 7) / 8)), dim3(256), 0, s,
-                     x, x_stride, xcls, tokens, out, rows, d, g, b, eps);
+  const int64_t groups = (rows + 7) / 8;
+  LnRows walk{0, 0, 0};
+  if (groups <= kLnGroups || NC > 4) {
+    hipLaunchKernelGGL((layernorm_bf16_kernel<NC, false>), dim3((unsigned)groups), dim3(256), 0, s,
+                       x, x_stride, xcls, tokens, walk, out, rows, d, g, b, eps);
+    return hipGetLastError();
+  }
+  // As many workgroups as stay resident together, each with the same count of
+  // rows give or take one.
+  const int64_t each = (groups + kLnGroups - 1) / kLnGroups, grid = (groups + each - 1) / each;
+  walk.step = grid * 8;
+  if (xcls != nullptr) {
+    walk.step_q = walk.step / tokens;
+    walk.step_r = (int)(walk.step - walk.step_q * tokens);
+  }
+  constexpr bool kWalk = NC <= 4;  // (past that not reached)
+  hipLaunchKernelGGL((layernorm_bf16_kernel<NC, kWalk>), dim3((unsigned)grid), dim3(256), 0, s, x,
+                     x_stride, xcls, tokens, walk, out, rows, d, g, b, eps);
   return hipGetLastError();
 }
 
