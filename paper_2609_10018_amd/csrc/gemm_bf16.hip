@@ -42,11 +42,11 @@
 #include "common.h"
 #include "gemm_small.h"
 #include "kernels.h"
+#include "lds_load.h"
 
 namespace elasto {
 namespace {
 
-typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) void global_void;
 
 constexpr int kBK = 64;        // K per step
@@ -226,25 +226,7 @@ __device__ __forceinline__ float2 ln_factors(const LnStat& st, float eps) {
   return make_float2(rstd, -rstd * st.mean);
 }
 
-// Buffer descriptor word 3 for raw (unswizzled, stride 0) buffers on CDNA.
-constexpr int kRsrcWord3 = 0x00020000;
-constexpr unsigned kOutOfRange = 0x80000000u;  // at or past every buffer's size
-
 __device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
-
-// Wait until at most N vector-memory operations of this wave are in flight
-// and every LDS operation has completed.
-template <int N>
-__device__ __forceinline__ void wait_vm_lds() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4));
-}
-
-// Wait until every LDS operation of this wave has completed (vector memory
-// operations may still be in flight).
-__device__ __forceinline__ void wait_lds() {
-  __builtin_amdgcn_s_waitcnt(0xF | (0x7 << 4) | (0x0 << 8) | (0x3 << 14));
-}
 
 // Store 8 floats (the first `valid` of them when the chunk is ragged).
 __device__ __forceinline__ void store_f32x8(float* cp, const float* v, bool full, int valid) {
@@ -2000,11 +1982,19 @@ hipError_t launch_conv_bf16(const ConvArgs& a, hipStream_t s) {
   const int per = (int)std::min<int64_t>(a.batch, limit / img_bytes);
   for (int b0 = 0; b0 < a.batch; b0 += per) {
     const int nb = std::min(per, a.batch - b0);
+    const uint16_t* x = static_cast<const uint16_t*>(a.x) + (int64_t)b0 * a.H * a.W * a.Cs;
+    uint16_t* y = static_cast<uint16_t*>(a.C) + (int64_t)b0 * Ho * Wo * a.ldc;
+    if (conv3x3_applies(a)) {
+      if (a.plan != 0) return hipErrorNotSupported;  // its tiles follow from the shape
+      const hipError_t e = launch_conv3x3(a, x, nb, w_bytes, y, s);
+      if (e != hipSuccess) return e;
+      continue;
+    }
     Params p{};
-    p.A = static_cast<const uint16_t*>(a.x) + (int64_t)b0 * a.H * a.W * a.Cs;
+    p.A = x;
     p.W = static_cast<const uint16_t*>(a.weight);
     p.ldw = a.ldw;
-    p.C = static_cast<uint16_t*>(a.C) + (int64_t)b0 * Ho * Wo * a.ldc;
+    p.C = y;
     p.ldc = a.ldc;
     p.bias = a.bias;
     p.M = nb * Ho * Wo;

@@ -139,6 +139,12 @@ struct ConvArgs {
   int plan = 0;  // as GemmArgs::plan (the persistent and four-stage plans do not apply)
 };
 hipError_t launch_conv_bf16(const ConvArgs& a, hipStream_t s);
+
+// The 3x3, stride 1 convolutions that launch_conv_bf16 hands to conv3x3.hip,
+// one run of images (input below 2 GiB) a call.
+bool conv3x3_applies(const ConvArgs& a);
+hipError_t launch_conv3x3(const ConvArgs& a, const void* x, int images, int64_t w_bytes, void* out,
+                          hipStream_t s);
 hipError_t launch_gemm_f32(Epi epi, const GemmArgs& a, hipStream_t s);
 
 // out[r] = LN(x[r]) over d features; x row stride x_stride, out contiguous.
