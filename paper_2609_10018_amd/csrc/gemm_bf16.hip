@@ -291,7 +291,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(Params p) 
   constexpr int APW = ABLK / NW;
   static_assert(ABLK % NW == 0 && BBLK % NW == 0, "blocks must split evenly over waves");
   constexpr int STAGE = (BM + BN) * kRowBytes;
-  constexpr int EPI_BYTES = (BM > 128 ? 128 : BM) * (BN + 8) * 4;
+  constexpr int SR = BM % 128 == 0 ? 128 : WTM;  // rows of an epilogue pass
+  constexpr int EPI_BYTES = SR * (BN + 8) * 4;
   constexpr int SMEM_MAIN = STAGES * STAGE > EPI_BYTES ? STAGES * STAGE : EPI_BYTES;
   constexpr bool LN_CONSUMER = E == Epi::Bias || E == Epi::BiasGelu;
   constexpr bool LN_PRODUCER = E == Epi::BiasResid || E == Epi::Patch;
@@ -592,7 +593,6 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(Params p) 
   // so that bias, activation, residual and conversion run on 8-column chunks
   // with 16-byte global loads and stores.  D layout of a 32x32 MFMA block:
   // element e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32.
-  constexpr int SR = BM > 128 ? 128 : BM;  // rows per pass
   constexpr int SS = BN + 8;                // staged row stride (floats): the two
                                             // half-waves land on distinct banks
   constexpr int CPR = BN / 8;               // 8-column chunks per row
@@ -1684,6 +1684,10 @@ hipError_t launch_forced(const Params& p, hipStream_t s) {
   }
 }
 
+// Epilogues with 192x256 tiles (the others' launches are not of that size).
+template <Epi E, bool CONV>
+constexpr bool kTile192 = !CONV && E != Epi::Patch && E != Epi::BiasF32;
+
 template <Epi E, bool CONV = false>
 hipError_t launch_epi(const Params& p, hipStream_t s) {
   if (p.plan != 0) return launch_forced<E, CONV>(p, s);
@@ -1714,6 +1718,20 @@ hipError_t launch_epi(const Params& p, hipStream_t s) {
     const double t = rounds(tiles) * cfgs[i].rel;
     if (t < best_t - 1e-9) { best_t = t; best = i; }
   }
+  // 192x256 where more, smaller tiles leave fewer CUs idle in the same rounds
+  // (12608 x 768: 198 tiles instead of 150).  us against 256x256, residual
+  // epilogue: K 3072 87.6 -> 76.6, K 768 31.8 -> 30.3; 9456 x 1024 x 1024 35.7 ->
+  // 30.7; 5000 x 2000 x 1000 39.0 -> 34.4.  Not against the persistent kernel
+  // with short K (12608 x 768 x 768, bias: 27.1 against 28.4), and slower with a
+  // round more (25216 x 384 x 1536: 48.9 against 72.8), which the count says.
+  constexpr double kRel192x256 = 0.88;
+  bool tall = false;
+  if constexpr (kTile192<E, CONV>) {
+    const int64_t tiles = (int64_t)((p.M + 191) / 192) * ((p.N + 255) / 256);
+    const double t = rounds(tiles) * kRel192x256;
+    tall = t < best_t - 1e-9 && !(p.K <= 1024 && persistent_default<E>(p));
+    if (tall) best_t = t;
+  }
   const int64_t tn = (p.N + 255) / 256, total = tn * ((p.M + 255) / 256);
   const int64_t head_rows = (total / kCUs) * kCUs / tn * 256;  // rows in whole rounds
   if (head_rows > 0 && head_rows < p.M) {
@@ -1739,6 +1757,9 @@ hipError_t launch_epi(const Params& p, hipStream_t s) {
       }
       return launch_cfg<128, 256, 2, 4, E, CONV>(p, (int)head_rows, s);
     }
+  }
+  if constexpr (kTile192<E, CONV>) {
+    if (tall) return launch_cfg<192, 256, 2, 4, E, CONV>(p, 0, s);
   }
   switch (best) {
     case 0:

@@ -142,3 +142,15 @@ def test_small_linear_f32(epi, M, N, K, lda):
 def test_linear_in_less_than_a_round_of_128_tiles(epi, M, N, K, ld):
     """Too large for 64x64 tiles in one round, fewer 128x128 tiles than CUs."""
     test_small_linear(epi, M, N, K, ld, ld)
+
+
+@pytest.mark.parametrize("M,N,K,ld", [(4000, 2200, 200, 200), (3901, 2301, 72, 72), (4033, 2176, 1088, 1088)])
+@pytest.mark.parametrize("epi", [ffi.EPI_BIAS, ffi.EPI_BIAS_GELU, ffi.EPI_BIAS_RESID])
+def test_linear_in_192_row_tiles(epi, M, N, K, ld):
+    """More 192x256 tiles than 256x256 ones in the same round."""
+    test_small_linear(epi, M, N, K, ld, ld)
+
+
+@pytest.mark.parametrize("M,d,N,K,tokens", [(4200, 2112, 2200, 1100, 197), (4001, 2240, 2184, 1090, 0)])
+def test_folded_layernorm_in_192_row_tiles(M, d, N, K, tokens):
+    test_small_folded_layernorm(M, d, N, K, tokens)
