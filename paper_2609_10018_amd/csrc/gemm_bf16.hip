@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_bf16_kernel(Params p) 
   constexpr int APW = ABLK / NW;
   static_assert(ABLK % NW == 0 && BBLK % NW == 0, "blocks must split evenly over waves");
   constexpr int STAGE = (BM + BN) * kRowBytes;
-  constexpr int SR = BM % 128 == 0 ? 128 : WTM;  // rows of an epilogue pass
+  constexpr int SR = BM % 128 == 0 ? 128 : BM > 128 ? WTM : BM;  // rows of an epilogue pass
   constexpr int EPI_BYTES = SR * (BN + 8) * 4;
   constexpr int SMEM_MAIN = STAGES * STAGE > EPI_BYTES ? STAGES * STAGE : EPI_BYTES;
   constexpr bool LN_CONSUMER = E == Epi::Bias || E == Epi::BiasGelu;
@@ -1659,6 +1659,20 @@ hipError_t launch_persistent(const Params& p0, int rows, hipStream_t s) {
   }
 }
 
+// 64-column tiles.  Their GEMMs stream A (bound by HBM), so small tiles, three
+// or more on a CU, whose loads run under each other's epilogues: 802816 x 48 x
+// 256 116 us in 256x64 tiles (two on a CU), 106 in 128x64; K 64: 50.1, 42.3;
+// 200704 x 88 x 512: 53.1, 48.6; 50432 x 64 x 192: 8.5, 7.5.  A ragged K, whose
+// last step goes through registers, takes 64x64 (100000 x 24 x 300: 17.4 us,
+// 18.7 in 128x64, 16.0 in 64x64).  Convolutions, whose address arithmetic a
+// wider tile shares, keep 256x64.
+template <Epi E, bool CONV>
+hipError_t launch_narrow(const Params& p, hipStream_t s) {
+  if constexpr (CONV) return launch_cfg<256, 64, 4, 1, E, CONV>(p, 0, s);
+  else if (p.K % kBK == 0) return launch_cfg<128, 64, 2, 2, E, CONV>(p, 0, s);
+  else return launch_cfg<64, 64, 2, 2, E, CONV>(p, 0, s);
+}
+
 // One launch of the tile plan p.plan (see kTilePlans).
 template <Epi E, bool CONV>
 hipError_t launch_forced(const Params& p, hipStream_t s) {
@@ -1666,7 +1680,7 @@ hipError_t launch_forced(const Params& p, hipStream_t s) {
     case 1: return launch_cfg<256, 256, 2, 4, E, CONV>(p, 0, s);
     case 2: return launch_cfg<256, 128, 2, 2, E, CONV>(p, 0, s);
     case 3: return launch_cfg<128, 128, 2, 2, E, CONV>(p, 0, s);
-    case 4: return launch_cfg<256, 64, 4, 1, E, CONV>(p, 0, s);
+    case 4: return launch_narrow<E, CONV>(p, s);
     case 5:
       if constexpr (!CONV && (E == Epi::Bias || E == Epi::BiasGelu || E == Epi::BiasResid)) {
         if (p.K % kBK == 0 && p.K / kBK >= 4) return launch_cfg<128, 128, 2, 2, E, CONV, 4>(p, 0, s);
@@ -1707,9 +1721,10 @@ hipError_t launch_epi(const Params& p, hipStream_t s) {
   constexpr double kRel128x256 = 0.6, kRel128x128 = 0.36;
   auto rounds = [](int64_t tiles) { return (double)((tiles + kCUs - 1) / kCUs); };
   struct Cfg { int bm, bn; double rel; };
-  // 256x64 (four waves stacked along M) only for outputs at most 64 wide,
-  // where wider tiles would leave half their columns idle.
-  const Cfg cfgs[4] = {{256, 256, 1.0}, {256, 128, 0.62}, {128, 128, 0.36}, {256, 64, 0.3}};
+  // 64-column tiles (launch_narrow) only for outputs at most 64 wide, where
+  // wider tiles would leave half their columns idle.
+  const Cfg narrow = CONV ? Cfg{256, 64, 0.3} : p.K % kBK == 0 ? Cfg{128, 64, 0.135} : Cfg{64, 64, 0.075};
+  const Cfg cfgs[4] = {{256, 256, 1.0}, {256, 128, 0.62}, {128, 128, 0.36}, narrow};
   const int ncfg = p.N <= 64 ? 4 : 3;
   int best = 0;
   double best_t = 1e300;
@@ -1783,7 +1798,7 @@ hipError_t launch_epi(const Params& p, hipStream_t s) {
         }
       }
       return launch_cfg<128, 128, 2, 2, E, CONV>(p, 0, s);
-    default: return launch_cfg<256, 64, 4, 1, E, CONV>(p, 0, s);
+    default: return launch_narrow<E, CONV>(p, s);
   }
 }
 

@@ -88,7 +88,8 @@ struct GemmArgs {
 };
 
 // Tile plans a caller may force (GemmArgs::plan, ConvArgs::plan): 1 256x256,
-// 2 256x128, 3 128x128, 4 256x64, 5 128x128 with four LDS stages (bf16
+// 2 256x128, 3 128x128, 4 64 columns (128x64, with a ragged K 64x64;
+// convolutions 256x64), 5 128x128 with four LDS stages (bf16
 // Bias / BiasGelu / BiasResid, no implicit convolution, K a multiple of 64
 // and >= 256), 6 the persistent 256x256 kernel (where the planner may use
 // it).  These plans walk K in the same order with the same MFMA
@@ -136,7 +137,8 @@ struct ConvArgs {
   int N = 0;
   bool relu = false;
   int row_window = 0;
-  int plan = 0;  // as GemmArgs::plan (the persistent and four-stage plans do not apply)
+  int plan = 0;  // as GemmArgs::plan (the persistent and four-stage plans do not apply, and to
+                 // the convolutions of conv3x3.hip none but 0)
 };
 hipError_t launch_conv_bf16(const ConvArgs& a, hipStream_t s);
 

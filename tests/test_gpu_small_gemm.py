@@ -154,3 +154,17 @@ def test_linear_in_192_row_tiles(epi, M, N, K, ld):
 @pytest.mark.parametrize("M,d,N,K,tokens", [(4200, 2112, 2200, 1100, 197), (4001, 2240, 2184, 1090, 0)])
 def test_folded_layernorm_in_192_row_tiles(M, d, N, K, tokens):
     test_small_folded_layernorm(M, d, N, K, tokens)
+
+
+@pytest.mark.parametrize("M,N,K,ld", [(16500, 64, 64, 64), (16449, 40, 128, 136), (16500, 23, 100, 104),
+                                      (20001, 64, 328, 328)])
+@pytest.mark.parametrize("epi", [ffi.EPI_BIAS, ffi.EPI_BIAS_GELU, ffi.EPI_BIAS_RESID,
+                                 ffi.EPI_BIAS_F32OUT])
+def test_linear_of_few_columns(epi, M, N, K, ld):
+    """At most 64 columns over more rows than one round of 64x64 tiles."""
+    test_small_linear(epi, M, N, K, ld, ld)
+
+
+@pytest.mark.parametrize("K", [64, 72])
+def test_folded_layernorm_of_few_columns(K):
+    test_small_folded_layernorm(16500, 64, 56, K, 197)
