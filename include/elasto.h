@@ -537,8 +537,8 @@ elasto_status_t elasto_cnn_validate(const elasto_cnn_config_t* cfg, const elasto
  * half-batch forwards, and whether a mode runs as two half-batch forwards on
  * two streams (about two seconds for ResNet-50 at 256 images; synchronises
  * the device), kept per process for handles of the same shapes; forwards of
- * more than max_batch / 2 images run as chosen.  Every choice gives
- * bit-identical outputs. */
+ * more than max_batch / 2 images run as chosen.  Every choice, every batch
+ * size and every max_batch give an image bit-identical logits. */
 elasto_status_t elasto_cnn_create(const elasto_cnn_config_t* cfg, const elasto_cnn_weights_t* w,
                                   const elasto_cnn_table_t* table, elasto_cnn_t* out);
 elasto_status_t elasto_cnn_destroy(elasto_cnn_t h);

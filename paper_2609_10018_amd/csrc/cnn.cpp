@@ -27,10 +27,12 @@
 // are independent, so the halves only fork and join): a kernel's last
 // partial round of tiles then overlaps the other half's kernels.  The split
 // is kept where it is faster by the margin.  The choices are kept per
-// process for handles of the same shapes (plans.h).  None of these GEMMs has LayerNorm work, so every
-// plan and the split give bit-identical outputs: the choices change the
-// speed only.  Forwards of more than half of max_batch images use them;
-// smaller ones run whole with the planner.
+// process for handles of the same shapes (plans.h).  None of these GEMMs has
+// LayerNorm work and all of them ask the planner for the one order of sums of
+// the tile plans (GemmArgs::one_order), so every plan, the split, every batch
+// size and every handle of a model give an image bit-identical logits: the
+// choices change the speed only.  Forwards of more than half of max_batch
+// images use them; smaller ones run whole with the planner.
 #include <hip/hip_runtime.h>
 #include <string.h>
 

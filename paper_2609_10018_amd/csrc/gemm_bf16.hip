@@ -1556,10 +1556,12 @@ hipError_t launch_cfg(const Params& p0, int row0, hipStream_t s) {
 }
 
 // Whether the kernel for few tiles takes the launch (small_pick), and its
-// launch.  A producer of LayerNorm statistics needs tiles of 64 columns.
+// launch.  A producer of LayerNorm statistics needs tiles of 64 columns.  Its
+// waves share out K, so never where one order of sums is asked for.
 constexpr SmallShape kSmall[] = {{1, 2}, {2, 2}, {2, 4}, {4, 4}};
 constexpr SmallShape kSmallSegments[] = {{1, 4}, {2, 4}, {4, 4}};
 inline int small_choice(const Params& p) {
+  if (p.one_order) return -1;
   return p.ln_out != nullptr ? small_pick(kSmallSegments, p.M, p.N) : small_pick(kSmall, p.M, p.N);
 }
 template <Epi E, int TMB, int TNB, int D>
@@ -1946,7 +1948,7 @@ hipError_t launch_gemm_bf16(Epi epi, const GemmArgs& a, hipStream_t s) {
   // in as many chunks as the planner's model chooses (plan 0) or as a split
   // plan forces (kSplitPlan0 and up); a forced tile plan never splits.
   const bool split_ok = a.ws != nullptr && a.ksplit <= 1 && !a.relu && a.aux == nullptr &&
-                        p.bias != nullptr &&
+                        p.bias != nullptr && !a.one_order &&
                         (epi == Epi::Bias || epi == Epi::BiasGelu || epi == Epi::BiasResid);
   int ksplit = 1, kchunk = 0;
   if (a.plan >= kSplitPlan0) {

@@ -82,8 +82,10 @@ struct GemmArgs {
   // runs that one configuration, or returns hipErrorNotSupported where it
   // cannot take these arguments.
   int plan = 0;
-  // Tiled launches of plan 0 sum K in the one order of plans 1-6 (the CNN: its
-  // outputs then do not depend on which tile plan the tuning chose).
+  // Plan 0 sums K in the one order of plans 1-6 whatever the launch's size:
+  // neither the kernel for few tiles nor two groups of waves nor a split K
+  // (the CNN: its outputs then depend neither on the plans that the timing
+  // chose nor on the batch or the part of it an image falls in).
   bool one_order = false;
 };
 
@@ -95,11 +97,12 @@ struct GemmArgs {
 // it).  These plans walk K in the same order with the same MFMA
 // instruction, so for a GEMM with no LayerNorm work (ln_in, ln_out) and no
 // class-token rows (ccls) the outputs are bit-identical whatever the plan.
-// Plan 0 takes the kernel of gemm_small.h for launches whose 64x64 tiles (or
-// smaller ones) all run at once; its sums are split over four waves, so its
-// bits differ from the other plans', but not with the launch's size.  Without
-// one_order it also splits the steps of 128x128 tiles that fill less than a
-// round over two groups of waves.
+// Without one_order, plan 0 takes the kernel of gemm_small.h for launches whose
+// 64x64 tiles (or smaller ones) all run at once, and splits the steps of 128x128
+// tiles that fill less than a round over two groups of waves.  Both sum K in
+// orders of their own (gemm_small.h: the same one for every tile shape), so
+// plan 0's bits differ from the other plans' there, and a row's bits change
+// where M takes a launch from one of these kernels to another.
 // Plans kSplitPlan0 + i split K into about kSplitChunks[i] chunks (bf16 Bias /
 // BiasGelu / BiasResid with a workspace, where the 128x128 tiles would fill
 // under half the CUs and plan 0 has no one-round kernel; the partials are

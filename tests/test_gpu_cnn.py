@@ -132,6 +132,33 @@ def test_resnet50_tile_plans_do_not_change_outputs():
         np.testing.assert_array_equal(full[h:], second.cpu().numpy())
 
 
+@pytest.mark.parametrize("max_batch", [32, 64])
+def test_resnet50_bits_do_not_depend_on_plans_or_batch(max_batch):
+    """Small tuned handles, where 1x1 layers and the classifier have few tiles: the
+    whole batch (tuned plans, one or two streams) against its halves and single
+    images (the planner), and the next handle's whole batch, bit for bit in every
+    mode."""
+    n = Net("resnet50", max_batch=max_batch)
+    h = max_batch // 2
+    half = torch.empty((h, n.cfg.num_classes), dtype=torch.float32, device="cuda")
+    one = torch.empty((1, n.cfg.num_classes), dtype=torch.float32, device="cuda")
+    for k in range(n.table.num_modes):
+        full = n.run(k)
+        np.testing.assert_array_equal(n.run(k), full)
+        np.testing.assert_array_equal(n.run(k, h + 1), full[:h + 1])
+        for i in (0, h):
+            n.net.forward(n.xd[i:i + h].contiguous(), half)
+            np.testing.assert_array_equal(half.cpu().numpy(), full[i:i + h])
+        n.net.forward(n.xd[-1:].clone(), one)
+        np.testing.assert_array_equal(one.cpu().numpy(), full[-1:])
+    n.net.close()
+    if max_batch == 32:  # the same images in the larger handle
+        m = Net("resnet50", max_batch=64)
+        assert torch.equal(m.xd[:32], n.xd)
+        np.testing.assert_array_equal(m.run(k)[:32], full)
+        m.net.close()
+
+
 def test_cnn_mode_info_matches_cost_model():
     from paper_2609_10018_amd import cost
     n = net("resnet50")
