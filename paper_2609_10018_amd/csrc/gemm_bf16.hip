@@ -1668,11 +1668,26 @@ hipError_t launch_persistent(const Params& p0, int rows, hipStream_t s) {
 // last step goes through registers, takes 64x64 (100000 x 24 x 300: 17.4 us,
 // 18.7 in 128x64, 16.0 in 64x64).  Convolutions, whose address arithmetic a
 // wider tile shares, keep 256x64.
+// N > 64 comes here as forced plan 4 only.  Launches of few rounds gain from
+// small tiles there too (whole forwards of ViT-B, tuned with them and with
+// 256x64: 8 images 0.59 and 0.64 ms in mode 4, 32 images 0.80 and 0.87).  Past
+// 12 64x64 tiles a CU 64 columns are not worth offering for themselves (best
+// case, the patch embedding of 128 images: 61.2 us, plan 3 62.4), but which of
+// them the tuning times beside the other plans matters: with the small tiles,
+// or with none, the planner's head and tail launches time 2 us less than with
+// 256x64 (25216 x 768 x 460: 47.5 and 49.6 us, plan 6 47.6 in both), the tuning
+// takes them for fc2 of half of 256 images, and inside a forward on two
+// streams they lose: ViT-B mode 4 2.75 ms with 256x64, 2.90 to 3.24 without.
 template <Epi E, bool CONV>
 hipError_t launch_narrow(const Params& p, hipStream_t s) {
-  if constexpr (CONV) return launch_cfg<256, 64, 4, 1, E, CONV>(p, 0, s);
-  else if (p.K % kBK == 0) return launch_cfg<128, 64, 2, 2, E, CONV>(p, 0, s);
-  else return launch_cfg<64, 64, 2, 2, E, CONV>(p, 0, s);
+  constexpr int64_t kMostSmall = 12 * 256;
+  if constexpr (!CONV) {
+    if (p.N <= 64 || (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64) <= kMostSmall) {
+      return p.K % kBK == 0 ? launch_cfg<128, 64, 2, 2, E, CONV>(p, 0, s)
+                            : launch_cfg<64, 64, 2, 2, E, CONV>(p, 0, s);
+    }
+  }
+  return launch_cfg<256, 64, 4, 1, E, CONV>(p, 0, s);
 }
 
 // One launch of the tile plan p.plan (see kTilePlans).

@@ -91,7 +91,7 @@ struct GemmArgs {
 
 // Tile plans a caller may force (GemmArgs::plan, ConvArgs::plan): 1 256x256,
 // 2 256x128, 3 128x128, 4 64 columns (128x64, with a ragged K 64x64;
-// convolutions 256x64), 5 128x128 with four LDS stages (bf16
+// convolutions and large launches of N > 64 256x64), 5 128x128 with four LDS stages (bf16
 // Bias / BiasGelu / BiasResid, no implicit convolution, K a multiple of 64
 // and >= 256), 6 the persistent 256x256 kernel (where the planner may use
 // it).  These plans walk K in the same order with the same MFMA
