@@ -221,17 +221,26 @@ __global__ __launch_bounds__(kThreads, 2) void conv3x3_kernel(C3Params p) {
   }
 }
 
+// Tiles for W > 31 too: not 256x96, which would be alone on its CU (162 against
+// 82 us for 256 x 56x56 x 64).
+template <int BM, int BN>
+constexpr bool kWideTile = !(BM == 256 && BN == 96);
+
 template <int BM, int BN, int WM, int WN>
 hipError_t launch_tile(C3Params p, hipStream_t s) {
   p.tiles_n = (p.N + BN - 1) / BN;
   const int64_t tiles = (int64_t)((p.M + BM - 1) / BM) * p.tiles_n;
   if (tiles > INT32_MAX) return hipErrorInvalidValue;
-  if (p.W <= 31)
+  if (p.W <= 31) {
     hipLaunchKernelGGL((conv3x3_kernel<BM, BN, WM, WN, BM / 64 + 1>), dim3((unsigned)tiles),
                        dim3(kThreads), 0, s, p);
-  else
-    hipLaunchKernelGGL((conv3x3_kernel<BM, BN, WM, WN, BM / 64 + 2>), dim3((unsigned)tiles),
-                       dim3(kThreads), 0, s, p);
+  } else {
+    if constexpr (kWideTile<BM, BN>)
+      hipLaunchKernelGGL((conv3x3_kernel<BM, BN, WM, WN, BM / 64 + 2>), dim3((unsigned)tiles),
+                         dim3(kThreads), 0, s, p);
+    else
+      return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
@@ -267,9 +276,7 @@ hipError_t launch_conv3x3(const ConvArgs& a, const void* x, int images, int64_t 
   // in microseconds, fitted to 22 layers of 1 to 256 images (7x7 to 56x56, 16
   // to 512 channels); the choice is within 9% of the best tile on all of them.
   // 96 outputs a wave spend a quarter less time on 88 than two tiles of 64 do
-  // (64 x 28x28, 88 channels: 15.2 and 17.1 us), and lose where N fills 64s;
-  // with W > 31 a 256 x 96 tile leaves no room for a second on its CU (162
-  // against 82 us).
+  // (64 x 28x28, 88 channels: 15.2 and 17.1 us), and lose where N fills 64s.
   constexpr struct { int bm, bn; double alone, shared, edge; } kTiles[] = {
       {256, 64, 0.84, 0.63, 2.6}, {256, 96, 1.15, 1.02, 2.8}, {128, 64, 0.54, 0.37, 1.4},
       {128, 96, 0.65, 0.55, 2.0}, {64, 64, 0.36, 0.26, 0.7}};
@@ -279,7 +286,7 @@ hipError_t launch_conv3x3(const ConvArgs& a, const void* x, int images, int64_t 
   double best_t = 1e300;
   for (int i = 0; i < 5; ++i) {
     const auto& c = kTiles[i];
-    if (i == 1 && p.W > 31) continue;
+    if (p.W > 31 && i == 1) continue;  // kWideTile
     const int64_t tiles = (int64_t)((p.M + c.bm - 1) / c.bm) * ((p.N + c.bn - 1) / c.bn);
     const double each = (double)((tiles + kCUs - 1) / kCUs);
     const double t = steps * (each < 2 ? c.alone : each * c.shared) + each * c.edge;

@@ -92,8 +92,8 @@ struct Params {
   int64_t ldres;
   uint16_t* aux;
   int64_t ldaux;
-  // BiasF32 split-K: blockIdx.y = chunk of kchunk K-elements, partial
-  // product to C + chunk * c_split.
+  // BiasF32 split-K (launch_split): blockIdx.y = chunk of kchunk K-elements,
+  // partial product to C + chunk * c_split.
   int ksplit, kchunk;
   int64_t c_split;
   // LayerNorm folding (see GemmArgs): producer statistics out, consumer
@@ -270,7 +270,9 @@ __device__ __forceinline__ u32x4 mask_tail(u32x4 v, int kbeg, int kend) {
 
 // STAGES: LDS stages of the tile loads (2: the next K step in flight while
 // this one computes; 4: three steps in flight, for launches of few tiles whose
-// K chain is bound by the load latency; needs K % 64 == 0 and no CONV).
+// K chain is bound by the load latency; no CONV).  A ragged last step goes
+// through registers in either form: its loads, and so all earlier ones, are
+// back before its LDS stores, and no load follows it, so the counted waits hold.
 // KS: groups of WM x WN waves that share out the four 16-value quarters of every
 // step; the groups' sums are added in LDS before the epilogue.
 template <int BM, int BN, int WM, int WN, Epi E, bool CONV, int STAGES = 2, int KS = 1>
@@ -1614,7 +1616,7 @@ bool persistent_ok(const Params& p) {
     // ReLU (convolution blocks): on the Bias and BiasResid epilogues, not on
     // a folded-LayerNorm consumer.
     const bool relu_ok = !p.relu || (E != Epi::BiasGelu && p.ln_in == nullptr);
-    return p.bias != nullptr && relu_ok && p.aux == nullptr && p.ksplit <= 1 && p.K >= 1 && k_ok &&
+    return p.bias != nullptr && relu_ok && p.aux == nullptr && p.K >= 1 && k_ok &&
            p.N % 8 == 0 &&
            p.ldc % 8 == 0 && (int64_t)kTilePers * p.ldc * 2 < ((int64_t)1 << 31);
   }
@@ -1723,10 +1725,8 @@ template <Epi E, bool CONV = false>
 hipError_t launch_epi(const Params& p, hipStream_t s) {
   if (p.plan != 0) return launch_forced<E, CONV>(p, s);
   if constexpr (!CONV) {
-    if (p.ksplit <= 1) {
-      const int small = small_choice(p);
-      if (small >= 0) return launch_small<E>(p, small, s);
-    }
+    const int small = small_choice(p);
+    if (small >= 0) return launch_small<E>(p, small, s);
   }
   // Pick the launch plan that keeps the chip busiest.  Estimated time is the
   // number of rounds of concurrent workgroups (one per CU) times the relative
@@ -1807,7 +1807,7 @@ hipError_t launch_epi(const Params& p, hipStream_t s) {
       // are in another order than the other plans': not for one_order.
       if constexpr (!CONV && E != Epi::Patch) {
         const int64_t tiles = ((p.M + 127) / 128) * ((p.N + 127) / 128);
-        if (tiles < kCUs && p.ksplit <= 1 && !p.one_order)
+        if (tiles < kCUs && !p.one_order)
           return launch_cfg<128, 128, 2, 2, E, CONV, 4, 2>(p, 0, s);
         if constexpr (E == Epi::Bias || E == Epi::BiasGelu || E == Epi::BiasResid) {
           if (tiles < kCUs && p.K % kBK == 0 && p.K / kBK >= 4)
@@ -1935,9 +1935,6 @@ hipError_t launch_gemm_bf16(Epi epi, const GemmArgs& a, hipStream_t s) {
   p.ldres = a.ldres;
   p.aux = static_cast<uint16_t*>(a.aux);
   p.ldaux = a.ldaux;
-  p.ksplit = a.ksplit;
-  p.kchunk = a.kchunk;
-  p.c_split = a.c_split;
   p.ln_out = a.ln_out;
   p.ln_in = a.ln_in;
   p.ln_ld = a.ln_ld;
@@ -1950,9 +1947,6 @@ hipError_t launch_gemm_bf16(Epi epi, const GemmArgs& a, hipStream_t s) {
   if (a.ln_in != nullptr && (epi != Epi::Bias && epi != Epi::BiasGelu || a.ln_colsum == nullptr ||
                              a.ln_ld < nseg_k || a.ln_ld % 2 != 0 || !(a.ln_eps > 0.0f)))
     return hipErrorInvalidValue;
-  if (a.ksplit > 1 && (epi != Epi::BiasF32 || a.kchunk < kBK || a.kchunk % kBK != 0 ||
-                       (int64_t)(a.ksplit - 1) * a.kchunk >= a.K || a.c_split < (int64_t)a.M * a.ldc))
-    return hipErrorInvalidValue;
   if (epi == Epi::GeluBwd && (a.aux == nullptr || a.ldaux < a.N || a.ldaux % 8 != 0))
     return hipErrorInvalidValue;
   if (a.res != nullptr && (a.ldres < a.N || a.ldres % 8 != 0)) return hipErrorInvalidValue;
@@ -1962,8 +1956,8 @@ hipError_t launch_gemm_bf16(Epi epi, const GemmArgs& a, hipStream_t s) {
   // Small M: split K over more workgroups when the caller gave a workspace,
   // in as many chunks as the planner's model chooses (plan 0) or as a split
   // plan forces (kSplitPlan0 and up); a forced tile plan never splits.
-  const bool split_ok = a.ws != nullptr && a.ksplit <= 1 && !a.relu && a.aux == nullptr &&
-                        p.bias != nullptr && !a.one_order &&
+  const bool split_ok = a.ws != nullptr && !a.relu && a.aux == nullptr && p.bias != nullptr &&
+                        !a.one_order &&
                         (epi == Epi::Bias || epi == Epi::BiasGelu || epi == Epi::BiasResid);
   int ksplit = 1, kchunk = 0;
   if (a.plan >= kSplitPlan0) {

@@ -139,7 +139,7 @@ elasto_status_t elasto_growth_create(elasto_handle_t h, int32_t max_batch, elast
   // Per-mode plans: gradient arena offsets and update slices.
   std::vector<std::vector<GrowthSlice>> host_slices;
   std::vector<std::vector<TransposeJob>> host_jobs;
-  int64_t grad_max = 0, tiles_max = 0;
+  int64_t grad_max = 0;
   g->wt_w1 = (int64_t)Mh * D;
   g->wt_wo = g->wt_w1 + (int64_t)D * up8(Mh);
   g->wt_qkv = g->wt_wo + (int64_t)D * D;
@@ -167,8 +167,6 @@ elasto_status_t elasto_growth_create(elasto_handle_t h, int32_t max_batch, elast
         lp.fc1b = off; off += dm;
         lp.fc2w = off; off += (int64_t)D * dm;
         mp.layers.push_back(lp);
-        tiles_max = std::max(tiles_max, 2 * wgrad_tiles((int)dm, D) + wgrad_tiles((int)dq, D) +
-                                            wgrad_tiles(D, 64 * (lp.h - lp.hp)));
         auto job = [&](int id, int64_t out, int ldi, int ldo, int rows, int cols) {
           jobs.push_back(TransposeJob{h->lay.get(id, l).offset / 2, g->wt_stride * l + out, ldi, ldo,
                                       rows, cols});
@@ -204,8 +202,8 @@ elasto_status_t elasto_growth_create(elasto_handle_t h, int32_t max_batch, elast
     mp.nslices = (int)sl.size();
     host_slices.push_back(std::move(sl));
   }
-  // Split tiles of a layer's weight gradients.
-  g->part_floats = std::max<int64_t>(kWgradSlots, tiles_max) * 128 * 128;
+  // Split tiles of a layer's weight gradients (unsplit ones go to the arena).
+  g->part_floats = (int64_t)kWgradSlots * 128 * 128;
   g->bstride = std::max(3 * D, Mh);
 
   // One device block for everything.

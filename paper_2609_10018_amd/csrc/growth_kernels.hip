@@ -464,10 +464,6 @@ hipError_t launch_transposes_bf16(const TransposeJob* jobs, int njobs, int max_t
   return hipGetLastError();
 }
 
-int64_t wgrad_tiles(int ra, int rb) {  // at most, wherever the columns start
-  return (int64_t)((ra + 7 + kWT - 1) / kWT) * ((rb + 7 + kWT - 1) / kWT);
-}
-
 hipError_t launch_wgrad_bf16(const WgradArgs* probs, int n, int64_t M, float* part,
                              int64_t part_floats, float* bpart, int bstride, hipStream_t s) {
   if (n < 0 || n > kWgradMax || M >= ((int64_t)1 << 31)) return hipErrorInvalidValue;

@@ -46,10 +46,6 @@ struct GemmArgs {
   // BiasGelu: also store the pre-activation to aux (bf16); GeluBwd: read it.
   void* aux = nullptr;
   int64_t ldaux = 0;
-  // BiasF32 only: split K into ksplit chunks of kchunk (a multiple of 64);
-  // chunk i writes its partial product to C + i * c_split (fp32 elements).
-  int ksplit = 1, kchunk = 0;
-  int64_t c_split = 0;
   // LayerNorm folded into the GEMMs (bf16 path).
   // Producer (BiasResid, Patch): ln_out != nullptr also writes, for every
   // output row r and every 64-column segment j of [0, N), the pair (sum of
@@ -211,7 +207,6 @@ struct WgradArgs {
   float *out, *bias;
 };
 constexpr int kWgradMax = 4, kWgradSlots = 512, kWgradMaxSplit = 32;
-int64_t wgrad_tiles(int ra, int rb);  // tiles of 128 x 128 fp32 partials a problem takes at most
 hipError_t launch_wgrad_bf16(const WgradArgs* probs, int n, int64_t M, float* part,
                              int64_t part_floats, float* bpart, int bstride, hipStream_t s);
 // LayerNorm backward (gamma only; beta and gamma are not trained): from x

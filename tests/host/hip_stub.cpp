@@ -158,9 +158,6 @@ hipError_t launch_attention_bwd_bf16(const AttnBwdArgs&, hipStream_t) { return l
 hipError_t launch_transposes_bf16(const TransposeJob*, int, int, const void*, void*, hipStream_t) {
   return launch();
 }
-int64_t wgrad_tiles(int ra, int rb) {
-  return (int64_t)((ra + 7 + 127) / 128) * ((rb + 7 + 127) / 128);
-}
 hipError_t launch_wgrad_bf16(const WgradArgs*, int, int64_t, float*, int64_t, float*, int,
                              hipStream_t) {
   return launch();
