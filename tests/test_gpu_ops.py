@@ -223,11 +223,13 @@ def test_attention(dtype, B, T, h, hd, stride):
     assert (host(od)[:, h * hd:] == 0).all()
 
 
-# Implicit-GEMM convolution (elastic ResNet layers) against the oracle's fp64
-# conv2d.  Cases: ragged output width and rows, a channel prefix (ca < cs),
-# several 64-channel steps per tap, odd image sizes with stride 2, a
+# Convolutions (elastic ResNet layers) against the oracle's fp64 conv2d.  3x3,
+# stride 1, pad 1 with W <= 63 runs the kernel of conv3x3.hip, all others the
+# implicit GEMM.  Cases: ragged output width and rows, a channel prefix
+# (ca < cs), several 64-channel steps per tap, odd image sizes with stride 2, a
 # non-square kernel, the smallest channel count, enough 256x256 tiles for the
-# split launch, and channel counts of at most 32 (taps sharing a K step).
+# implicit GEMM's split launch (W 64), and channel counts of at most 32 (taps
+# sharing a K step).
 CONV_CASES = [
     # batch, H, W, cs, ca, kh, kw, stride, pad, wseg, n, ldy, relu
     (3, 14, 14, 64, 56, 3, 3, 1, 1, 64, 40, 48, True),
@@ -240,6 +242,12 @@ CONV_CASES = [
     (4, 56, 56, 64, 16, 3, 3, 2, 1, 64, 16, 16, True),
     (2, 14, 14, 64, 32, 3, 3, 1, 1, 64, 32, 32, True),
     (3, 7, 7, 24, 24, 3, 3, 1, 1, 24, 24, 24, False),
+    # implicit GEMM: 264 tiles of 256x256 (a whole round and a tail launch)
+    (17, 62, 64, 72, 64, 3, 3, 1, 1, 64, 256, 256, True),
+    (2, 15, 15, 128, 104, 3, 3, 2, 1, 136, 72, 72, False),
+    (1, 9, 64, 48, 40, 3, 3, 1, 1, 48, 40, 48, True),
+    (1, 6, 66, 24, 16, 3, 3, 1, 1, 24, 24, 24, True),
+    (2, 10, 12, 96, 72, 1, 1, 2, 0, 96, 104, 104, False),
 ]
 
 
@@ -276,8 +284,14 @@ def test_conv2d(case):
     np.testing.assert_array_equal(tail_after, tail_before)  # columns >= n untouched
 
 
-def test_conv2d_never_reads_inactive_channels():
-    case = CONV_CASES[0]
+# conv3x3.hip; the implicit GEMM with one tap and with several taps a K step, at
+# stride 2 and past the other kernel's widths, and in its split launch.
+POISON_CASES = [c for c in CONV_CASES if c[4] < c[3] and not (c[7] == 1 and c[2] <= 63)]
+
+
+@pytest.mark.parametrize("case", [CONV_CASES[0]] + POISON_CASES,
+                         ids=lambda c: f"{c[1]}x{c[2]}-c{c[4]}of{c[3]}-k{c[5]}s{c[7]}")
+def test_conv2d_never_reads_inactive_channels(case):
     clean, ref, _, _ = _conv_case(*case)
     poisoned, _, _, _ = _conv_case(*case, poison=True)
     assert np.isfinite(poisoned).all()
