@@ -23,6 +23,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import statistics
 import sys
 import time
@@ -39,12 +40,19 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_vit_b_b256.json")
 
 def kernel_source_hash() -> str:
     """Hash of the device code: every .hip source (kernels and their launch
-    planning) and the kernel headers; host-only sources are left out."""
+    planning) and the headers of its folder that they include; host-only sources
+    are left out."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2609_10018_amd", "csrc")
-    for f in sorted(os.listdir(csrc)):
-        if f.endswith(".hip") or f in ("kernels.h", "common.h"):
-            h.update(open(os.path.join(csrc, f), "rb").read())
+    names = {f for f in os.listdir(csrc) if f.endswith(".hip")}
+    todo = sorted(names)
+    while todo:
+        for inc in re.findall(r'#include "(\w+\.h)"', open(os.path.join(csrc, todo.pop())).read()):
+            if inc not in names:
+                names.add(inc)
+                todo.append(inc)
+    for f in sorted(names):
+        h.update(open(os.path.join(csrc, f), "rb").read())
     return h.hexdigest()[:16]
 
 
