@@ -60,6 +60,14 @@ def test_classify_persistent_and_folded_layernorm():
                      "head": 1}
 
 
+def test_classify_the_gemm_for_launches_of_few_tiles():
+    small = "void elasto::(anonymous namespace)::gemm_{}_small<(elasto::Epi){}, 1, 2{}>(elasto::(anonymous namespace)::{})"
+    bf = [small.format("bf16", e, ", 3", "Params") for e in range(5)]
+    assert pmc.classify([bf[4], bf[0], ATT, bf[2], bf[1], bf[2], LN, bf[3]]) == [
+        "patch", "qkv", "attn", "proj", "fc1", "fc2", "ln", "head"]
+    assert pmc.classify([small.format("f32", 3, "", "P32")]) == ["head"]
+
+
 def _write_counters(path, names, counters):
     os.makedirs(path, exist_ok=True)
     with open(os.path.join(path, "run_counter_collection.csv"), "w", newline="") as f:
