@@ -52,7 +52,11 @@ typedef enum {
  * MFMA with fp32 accumulation, fp32 LayerNorm / softmax / GELU, fp32 biases
  * and norm parameters; the class-token rows of the residual stream (the only
  * rows the logits depend on at the end) are kept in fp32.  FP32: fp32
- * everywhere (fp32 products and sums, no reduced-precision matrix mode). */
+ * everywhere (fp32 products and sums, no reduced-precision matrix mode).
+ * Results are deterministic, but the order in which a GEMM sums K follows from
+ * its size (and, in fp32, from the alignment of its rows): a row's results may
+ * differ between launches of different M, or batches, in the rounding of the
+ * fp32 sums (the elastic CNN keeps one order, see elasto_cnn_create). */
 typedef enum { ELASTO_FP32 = 0, ELASTO_BF16 = 1 } elasto_dtype_t;
 
 /* Model shape.  tokens T = (img/patch)^2 + 1, head_dim = dim/heads.

@@ -1756,6 +1756,8 @@ hipError_t launch_epi(const Params& p, hipStream_t s) {
   // 30.7; 5000 x 2000 x 1000 39.0 -> 34.4.  Not against the persistent kernel
   // with short K (12608 x 768 x 768, bias: 27.1 against 28.4), and slower with a
   // round more (25216 x 384 x 1536: 48.9 against 72.8), which the count says.
+  // Tile against tile the ratio was 0.86 to 0.95; with 0.88 none of 585 layers
+  // drawn over the supported sizes is slower than without these tiles.
   constexpr double kRel192x256 = 0.88;
   bool tall = false;
   if constexpr (kTile192<E, CONV>) {
@@ -1827,7 +1829,9 @@ hipError_t launch_epi(const Params& p, hipStream_t s) {
 // and 8 of ViT-B/16:
 //   one launch:  3 + 1.1 nk,
 //   c chunks:   11 + 1.1 ceil(nk / c) + c M N 8 bytes / 3.5 TB/s,
-// with at least two K steps a chunk and at most one workgroup per CU.
+// with at least two K steps a chunk and at most one workgroup per CU.  (The
+// first line is of one group of waves per tile; the two groups of launch_epi
+// take up to a sixth less, so a split close to it may lose to them.)
 // Returns the chunk count (1: no split) and the chunk length.
 int split_plan(const Params& p, int64_t ws_bytes, int* kchunk) {
   constexpr int kCUs = 256;

@@ -12,10 +12,11 @@
 // read, and value r of both halves is one MFMA.  LDS rows are 36 floats long,
 // so that 16 consecutive rows start on distinct groups of four banks.
 //
-// Bound: the matrix units (80% busy in a long K loop), and for short K the
-// loads before and the stores after a tile's loop.  6304 x 1152 x 384: 64 us,
-// 87 TFLOP/s (105 us on the vector ALU); 8000 x 3072 x 3072: 1180 us, 128
-// TFLOP/s (2251 us).
+// Bound: the matrix units (80% busy in the long K loop of 128x128 tiles, 66% in
+// 64x64 ones at K 1536), and for short K the loads before and the stores after a
+// tile's loop (53% at K 384).  6304 x 1152 x 384, 1782 64x64 tiles, at most four
+// on a CU: 59 us, 94 TFLOP/s (97 us on the vector ALU); 8000 x 3072 x 3072,
+// 128x128 tiles: 1190 us, 127 TFLOP/s (2270 us).
 #include <algorithm>
 #include <type_traits>
 

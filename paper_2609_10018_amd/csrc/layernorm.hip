@@ -25,14 +25,16 @@ __device__ __forceinline__ float half_sum(float v) {
 // lane; NC = ceil(d / 256) chunks per lane.
 //
 // Bound by HBM and the last-level cache.  A chunk's load was behind the test
-// for a class-token row, so the row's loads waited for one another: 36.3 us for
-// 50432 x 768; with the loads ahead of the test 25.6.  Rows that fill the chip
-// more than once (WALK): a half-wave walks rows `step` apart, the next row's
-// load in flight under the current row's sums, with g and b, four times a row's
-// bytes, staged in LDS once: 25.1 us, 25000 x 768 15.0 -> 13.1, 50432 x 384
-// 15.0 -> 13.4 (768 to 2048 workgroups: 24.9 to 27.6; 1280 is best or within
-// 2%).  Not for d > 1024, where the registers of a row ahead cost wavefronts
-// (50432 x 2048: 84.4 against 81.4).
+// for a class-token row, so the row's loads waited for one another: 50432 x 768
+// with class rows 37.5 us from HBM and 28.8 with its rows in the last-level
+// cache, now 31.7 and 24.6.  (The rest with rows in the cache:) the loads ahead
+// of the test gave most of it, 25.6.  Rows that fill the chip more than once
+// (WALK): a half-wave walks rows `step` apart, the next row's load in flight
+// under the current row's sums, with g and b, four times a row's bytes, staged
+// in LDS once: 25.1 us, 25000 x 768 15.0 -> 13.1, 50432 x 384 15.0 -> 13.4 (768
+// to 2048 workgroups: 24.9 to 27.6; 1280 is best or within 2%).  Not for
+// d > 1024, where the registers of a row ahead cost wavefronts (50432 x 2048:
+// 84.4 against 81.4).
 // step = step_q * tokens + step_r, so a row's image needs no division.
 struct LnRows {
   int64_t step, step_q;
