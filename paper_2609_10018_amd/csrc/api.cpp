@@ -576,8 +576,8 @@ elasto_status_t forward_parts(elasto_handle_t h, const void* images, int32_t bat
   if (!h->split[(size_t)k] || h->timed_class >= 0 || b2 < 1 || (b1 * img_bytes) % 16 != 0 ||
       !images || !logits)
     return forward_impl(h, images, batch, logits, hip_stream, act, h->plans.data() + o);
-  // Neither half gets the split-K workspace (they run at once, and each
-  // image's arithmetic must not depend on the half it falls in).
+  // Neither half gets the split-K workspace (they run at once, and with it in
+  // one of them an image's sums would depend on the half it falls in).
   Acts first = act;
   first.ws = nullptr;
   first.ws_bytes = 0;

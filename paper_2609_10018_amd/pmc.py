@@ -249,7 +249,7 @@ def summarize(out, cmds, mode):
     md = [
         f"# Kernel classes of the elastic ViT-B/16 forward — bf16, batch 256, DN mode {mode}",
         "",
-        "Commands (GPU box, run from `/tmp` with `TMPDIR=/tmp`; committed files only):",
+        "Commands (run from `/tmp` with `TMPDIR=/tmp`; committed files only):",
         "",
         "    PYTHONPATH=<repo> " + _portable(
             ["python", "-m", "paper_2609_10018_amd.pmc", "--out", out, "--mode", str(mode)],

@@ -132,6 +132,15 @@ def test_resnet50_tile_plans_do_not_change_outputs():
         np.testing.assert_array_equal(full[h:], second.cpu().numpy())
 
 
+@pytest.mark.parametrize("batch", [1, 31, 100])
+def test_resnet50_bits_do_not_depend_on_the_batch(batch):
+    """Partial batches of the large handle, which the planner runs, in the narrowest
+    and the widest mode."""
+    n = net("resnet50")
+    for k in (0, 5):
+        np.testing.assert_array_equal(n.run(k, batch), n.run(k)[:batch])
+
+
 @pytest.mark.parametrize("max_batch", [32, 64])
 def test_resnet50_bits_do_not_depend_on_plans_or_batch(max_batch):
     """Small tuned handles, where 1x1 layers and the classifier have few tiles: the
